@@ -963,11 +963,11 @@ LDS_COUNTERS = ["SQ_LDS_BANK_CONFLICT", "SQ_LDS_IDX_ACTIVE", "SQ_LDS_ADDR_CONFLI
 # The prefill-time kernels of the bench line: the SnapKV passes and selection
 # and the gather of the selected rows into a draft cache of their own.
 PREFILL_KERNELS = [
-    ("snapkv_pass_kernel", ", 0, 64", "softmax statistics over K", "k_once"),
-    ("snapkv_lse_kernel", "", "merge chunk statistics", None),
-    ("snapkv_pass_kernel", ", 1, 64", "votes (K again, votes written)", "k_once"),
-    ("snapkv_select", "", "pool, radix select, compaction", "votes"),
-    ("kv_gather", "", "listed rows into a draft cache", "gather"),
+    ("snapkv_pass_kernel", (", 0, 64", ", 0>("), "softmax statistics over K", "k_once"),
+    ("snapkv_lse_kernel", ("",), "merge chunk statistics", None),
+    ("snapkv_pass_kernel", (", 1, 64", ", 1>("), "votes (K again, votes written)", "k_once"),
+    ("snapkv_select", ("",), "pool, radix select, compaction", "votes"),
+    ("kv_gather", ("",), "listed rows into a draft cache", "gather"),
 ]
 
 
@@ -990,8 +990,8 @@ def summarize_prefill(trace_csv, fetch_csv, write_csv, bench_json, cmd):
     gib = float(1 << 30)
     scale = {c: gib / (calib[c] * 1024.0) for c in calib}
 
-    def pick(ds, key, sub):
-        return [d for d in ds if key in d["name"] and sub in d["name"]]
+    def pick(ds, key, subs):
+        return [d for d in ds if key in d["name"] and any(s in d["name"] for s in subs)]
 
     votes_written = None
     rows = []
@@ -1003,7 +1003,7 @@ def summarize_prefill(trace_csv, fetch_csv, write_csv, bench_json, cmd):
         rd = [d["FETCH_SIZE"] * 1024 * scale["FETCH_SIZE"] for d in pick(ctr["FETCH_SIZE"], key, sub)]
         wr = [d["WRITE_SIZE"] * 1024 * scale["WRITE_SIZE"] for d in pick(ctr["WRITE_SIZE"], key, sub)]
         r_b, w_b = sum(rd) / len(rd), sum(wr) / len(wr)
-        if key == "snapkv_pass_kernel" and sub == ", 1, 64":
+        if key == "snapkv_pass_kernel" and ", 1>(" in sub:
             votes_written = w_b
         rows.append((sorted({_short(d["name"]) for d in tr}), role, len(us), sum(us) / len(us),
                      min(us), max(us), r_b, w_b, a))

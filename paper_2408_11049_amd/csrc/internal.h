@@ -99,6 +99,8 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 // SnapKV selection: validation and the chunking of its two passes.
 constexpr int kSnapkvMaxRows = 256;  // G * n_obs
+constexpr int kSnapkvMinChunk = 128;    // keys: shortest chunk of a few units
+constexpr int kSnapkvLongChunk = 2048;  // keys: shortest chunk of many long units
 struct SnapkvPlan {
   int32_t G = 0, R = 0, TW = 0;
   int32_t n_units = 0;

@@ -239,18 +239,23 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 namespace {
 
-// Chunks of a range of U keys over n_units units: at least 2 * wg_per_cu
-// workgroups per compute unit (two rounds of wg_per_cu resident ones), never
-// below kMinChunkTokens per chunk.
-void split_range(int64_t U, int64_t n_units, int num_cus, int wg_per_cu, int32_t* n_chunks_out,
+// Chunks of a range of U keys over n_units units.  A few units are cut until
+// `fill` workgroups (what the device holds at once, about two rounds of it)
+// share the work, down to kSnapkvMinChunk keys: below that the prologue of a
+// chunk costs more than its keys (one prompt of 4000 tokens, 8 heads of 128
+// rows: 49 us at 1024 keys a chunk, 19.4 at 256, 15.2 at 128, 16.2 at 64).
+// Many long units are cut further, to sixteen workgroups per compute unit, so
+// that ragged lengths and the last round of workgroups even out, while a chunk
+// keeps kSnapkvLongChunk keys (64 prompts of 32768: 1700 us against 1764 with
+// two chunks a unit; 16 prompts of 16384, 64 rows: 185 us at 2048 keys a chunk
+// and 197 at 1024).
+void split_range(int64_t U, int64_t n_units, int64_t fill, int num_cus, int32_t* n_chunks_out,
                  int32_t* chunk_len_out) {
-  const int64_t slots = static_cast<int64_t>(num_cus > 0 ? num_cus : 256) * wg_per_cu;
   int64_t n_chunks = 1;
-  if (n_units > 0 && n_units < 2 * slots) {
-    n_chunks = ceil_div(2 * slots, n_units);
-    const int64_t cap = ceil_div(U, kMinChunkTokens);
-    if (n_chunks > cap) n_chunks = cap;
-    if (n_chunks < 1) n_chunks = 1;
+  if (n_units > 0) {
+    const int64_t few = std::min(ceil_div(fill, n_units), ceil_div(U, kSnapkvMinChunk));
+    const int64_t many = std::min(ceil_div(16 * int64_t{num_cus}, n_units), U / kSnapkvLongChunk);
+    n_chunks = std::max<int64_t>(1, std::max(few, many));
   }
   int64_t chunk_len = ceil_div(ceil_div(U > 0 ? U : 1, n_chunks), kTile) * kTile;
   n_chunks = ceil_div(U > 0 ? U : 1, chunk_len);
@@ -306,15 +311,18 @@ SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus) {
   p.R = p.G * a->n_obs;
   p.TW = p.R <= 64 ? 1 : (p.R <= 128 ? 2 : 4);
   p.n_units = a->num_seqs * a->num_kv_heads;
-  // Above 64 rows both passes take shorter chunks in several rounds of
-  // resident workgroups (measured at 128 rows and 512 units: 4096
-  // workgroups within 0.5% of 2048 and 2-6% faster than 1024, which leaves
-  // part of the last round's slots idle).
-  const int wg_per_cu = p.TW == 1 ? 2 : 8;
-  split_range(a->max_prompt_len, p.n_units, num_cus, wg_per_cu, &p.n_chunks_stats,
+  // Workgroups that fill the device: four per compute unit, fewer where a
+  // workgroup holds more of it -- the 129-256-row instances (eight waves in
+  // bf16: 63 us against 70 with four per compute unit on four 70B-shaped
+  // prompts of 5000-12000 tokens) and the fp32 ones, whose tiles take twice
+  // the LDS and registers (256 rows: one resident workgroup).
+  const int64_t cus = num_cus > 0 ? num_cus : 256;
+  const bool f32 = a->dtype == MD_F32;
+  const int64_t fill = cus * (p.R <= 64 ? 4 : (p.R <= 128 ? (f32 ? 2 : 4) : (f32 ? 1 : 2)));
+  split_range(a->max_prompt_len, p.n_units, fill, static_cast<int>(cus), &p.n_chunks_stats,
               &p.chunk_len_stats);
-  split_range(a->max_prompt_len - a->n_obs, p.n_units, num_cus, wg_per_cu, &p.n_chunks_votes,
-              &p.chunk_len_votes);
+  split_range(a->max_prompt_len - a->n_obs, p.n_units, fill, static_cast<int>(cus),
+              &p.n_chunks_votes, &p.chunk_len_votes);
   p.part_bytes = align_up(static_cast<size_t>(p.n_units) * p.n_chunks_stats * p.R * 4, 256);
   p.lse_bytes = align_up(static_cast<size_t>(p.n_units) * p.R * 4, 256);
   p.workspace_bytes = 2 * p.part_bytes + p.lse_bytes;

@@ -12,21 +12,22 @@
 //   32 observation positions, ascending.
 //
 // Kernels:
-//   snapkv_pass_kernel<PASS=0>  per (unit, key chunk): each observation row's
+//   snapkv_pass_kernel[_bf16]<PASS=0>  per (unit, key chunk): each observation row's
 //       running max and sum of exp over the chunk (softmax statistics);
 //   snapkv_lse_kernel           merges the chunks into one log2-sum-exp per row;
-//   snapkv_pass_kernel<PASS=1>  per (unit, prefix chunk): p = 2^(s - lse) and
+//   snapkv_pass_kernel[_bf16]<PASS=1>  per (unit, prefix chunk): p = 2^(s - lse) and
 //       the per-key sum over all rows: the raw votes;
 //   snapkv_select_kernel        per unit: pooled votes, radix select of the
 //       top keep, ordered compaction, plus the window.
-// In the pass kernels all G*n_obs rows of a unit share each 64-key tile,
-// loaded once into LDS as whole 256 B rows; each wave owns one or two 16-row
-// MFMA tiles of the rows and computes S = Q K^T on v_mfma_f32_16x16x32_bf16,
-// so each lane holds four rows of one key: a key's vote sums inside the lane
-// and across the wave's four lane groups, and the softmax statistics of a
-// row stay in its lanes until the chunk ends.  A tile costs one barrier: the
-// staging buffers and the per-wave vote sums alternate between two slots.
+// In the pass kernels all G*n_obs rows of a unit share each tile of keys,
+// loaded once into LDS as whole 256 B rows, and the scores are computed on
+// MFMA: 32 x 32 blocks in bf16, 16 x 16 in fp32.  A key's vote sums inside a
+// lane first and the softmax statistics of a row stay in its lanes until the
+// chunk ends.  A tile costs one barrier: the staging buffers and the per-wave
+// vote sums alternate between two slots.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "internal.h"
 #include "kernels.h"
@@ -37,11 +38,15 @@ namespace {
 
 typedef __bf16 sk_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sk_f32x4 __attribute__((ext_vector_type(4)));
+typedef float sk_f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t sk_u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kSkWaves = 4;      // up to 64 rows, and the votes pass at any row count
-constexpr int kSkWavesWide = 8;  // statistics pass, 65-256 rows: eight waves of one or two row tiles
-constexpr int kSkTile = 64;  // keys per tile: measured 5% faster than 32 keys, 128 slower
+// Waves of the fp32 passes: four up to 64 rows and in the votes pass, eight in
+// the statistics pass of 65-256 rows.
+constexpr int kSkWaves = 4;
+constexpr int kSkWavesWide = 8;
+constexpr int kSkVoteBuf = 1024;  // votes a workgroup buffers before it writes them
+constexpr int kSkTile = 64;  // keys per tile of the fp32 passes
 
 template <int D, bool BF16, int KT = kSkTile, int WV = kSkWaves>
 struct SkShape {
@@ -52,22 +57,128 @@ struct SkShape {
   static constexpr int NLD = KT / ROWS_PER_WG_LOAD;             // loads per lane per tile
   static constexpr int NB = KT / 16;                             // 16-key MFMA blocks per tile
   static constexpr int KROW = D * ES + 16;    // padded LDS row (odd multiple of 16 B)
+  static_assert(NLD * ROWS_PER_WG_LOAD == KT, "the tile's loads divide over the waves");
+};
+
+// Cooperative K tile load of a pass: thread -> key row (threadIdx / LPT) +
+// n * ROWS_PER_WG_LOAD, 16 B chunk threadIdx % LPT; a wave's lanes cover RPW
+// consecutive rows of each load.  Page ids are read ahead of the K loads that
+// use them, so a tile's loads never wait on a page-table read.
+//  WA (pages of at least RPW rows, or contiguous rows): a wave's RPW rows
+//    lie in one page, so their base address is wave-uniform scalar
+//    arithmetic and each lane adds a fixed 32-bit offset.  Rows past the
+//    range read the range's last key (contiguous) or stay inside the page
+//    of the group's first row; a group wholly past it reads element 0.
+//  !WA: each lane computes its own row address; keys past the range read
+//    element 0.  Keys past the range are masked either way.
+template <int D, bool BF16, bool PAGED, bool WA, int KT, int WV>
+struct SkLoader {
+  using SH = SkShape<D, BF16, KT, WV>;
+  static constexpr int RPW = 64 / SH::LPT;
+  const SnapkvParams& p;
+  const unsigned char* kbase;
+  const int32_t* ptab;
+  int64_t seq_off, head_off;
+  int v_begin, v_end, n_tiles, pmask, lane, wave_u;
+  uint32_t lane_chunk, lane_row, row_bytes, lane_off;
+
+  __device__ __forceinline__ SkLoader(const SnapkvParams& p_, int b, int hk, int v_begin_,
+                                      int v_end_, int n_tiles_, int lane_, int wave)
+      : p(p_), kbase(static_cast<const unsigned char*>(p_.k)),
+        ptab(PAGED ? p_.page_table + static_cast<int64_t>(b) * p_.max_pages : nullptr),
+        seq_off(static_cast<int64_t>(b) * p_.s_blk),
+        head_off(static_cast<int64_t>(hk) * p_.s_head), v_begin(v_begin_), v_end(v_end_),
+        n_tiles(n_tiles_), pmask((1 << p_.page_shift) - 1), lane(lane_),
+        wave_u(__builtin_amdgcn_readfirstlane(wave)),
+        lane_chunk(static_cast<uint32_t>(lane_ % SH::LPT) * 16),
+        lane_row(static_cast<uint32_t>(lane_ / SH::LPT)),
+        row_bytes(WA ? static_cast<uint32_t>(p_.s_tok * SH::ES) : 0),
+        lane_off(lane_row * row_bytes + lane_chunk) {}
+
+  // Page ids of a tile's loads: per lane (pid[n], !WA), or, with WA, one
+  // vector read in which lane n < NLD fetches load n's id (pid[0]), taken
+  // out with readlane where the load is issued.
+  __device__ __forceinline__ void load_pids(int (&pid)[SH::NLD], int tile) const {
+    if constexpr (PAGED) {
+      if constexpr (WA) {
+        const int n = lane % SH::NLD;
+        const int jw = v_begin + tile * KT + n * SH::ROWS_PER_WG_LOAD + wave_u * RPW;
+        const bool ok = tile < n_tiles && jw < v_end;
+        const int pg = ptab[ok ? (jw >> p.page_shift) : 0];
+        pid[0] = ok ? pg : -1;
+      } else {
+#pragma unroll
+        for (int n = 0; n < SH::NLD; ++n) {
+          const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
+          const int j = v_begin + tile * KT + tt;
+          const bool ok = tile < n_tiles && j < v_end;
+          pid[n] = ptab[ok ? (j >> p.page_shift) : 0];
+        }
+      }
+    }
+  }
+
+  __device__ __forceinline__ void load_tile(sk_u32x4 (&x)[SH::NLD], int tile,
+                                            const int (&pid)[SH::NLD]) const {
+    if (tile >= n_tiles) return;  // past the chunk: nothing to stage
+#pragma unroll
+    for (int n = 0; n < SH::NLD; ++n) {
+      int64_t off = 0;
+      uint32_t voff = lane_chunk;
+      if constexpr (WA) {
+        const int jw = v_begin + tile * KT + n * SH::ROWS_PER_WG_LOAD + wave_u * RPW;
+        voff = lane_off;
+        if constexpr (PAGED) {
+          const int pg = __builtin_amdgcn_readlane(pid[0], n);
+          const bool ok = pg >= 0 && pg < p.num_pages;
+          off = ok ? static_cast<int64_t>(pg) * p.s_blk +
+                         static_cast<int64_t>(jw & pmask) * p.s_tok + head_off
+                   : 0;
+          if (!ok) voff = lane_chunk;
+        } else {
+          const int jc = min(jw, v_end - 1);
+          off = seq_off + static_cast<int64_t>(jc) * p.s_tok + head_off;
+          if (jw + RPW > v_end)  // a group that reaches past the range
+            voff = min(lane_row, static_cast<uint32_t>(v_end - 1 - jc)) * row_bytes + lane_chunk;
+        }
+      } else {
+        const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
+        const int j = v_begin + tile * KT + tt;
+        bool ok = j < v_end;
+        if (PAGED) {
+          ok = ok && pid[n] >= 0 && pid[n] < p.num_pages;
+          off = ok ? static_cast<int64_t>(pid[n]) * p.s_blk +
+                         static_cast<int64_t>(j & pmask) * p.s_tok + head_off
+                   : 0;
+        } else {
+          off = ok ? seq_off + static_cast<int64_t>(j) * p.s_tok + head_off : 0;
+        }
+      }
+      x[n] = __builtin_nontemporal_load(
+          reinterpret_cast<const sk_u32x4*>(kbase + off * SH::ES + voff));
+    }
+  }
+
+  __device__ __forceinline__ void store_tile(const sk_u32x4 (&x)[SH::NLD],
+                                             unsigned char* tile_lds) const {
+#pragma unroll
+    for (int n = 0; n < SH::NLD; ++n) {
+      const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
+      *reinterpret_cast<sk_u32x4*>(tile_lds + tt * SH::KROW + (threadIdx.x % SH::LPT) * 16) = x[n];
+    }
+  }
 };
 
 }  // namespace
 
-// TW: 16-row tiles per wave, WV: waves (rows per workgroup = 16 * TW * WV); KT:
-// keys per tile.  The statistics pass runs 65-256 rows as eight waves of one
-// or two row tiles (more waves to cover the MFMA, exponential and load
-// latencies; the bf16 single-tile instance is held to 80 registers, six
-// waves per SIMD).  The votes pass keeps four waves (the whole call 10%
-// faster than with eight: half the LDS reads of each tile and of the
-// per-wave vote sums).
-template <int D, bool BF16, int TW, bool PAGED, bool WA, int PASS, int KT, int WV>
+// The fp32 passes.  TW: 16-row tiles per wave, WV: waves (rows per workgroup =
+// 16 * TW * WV); KT: keys per tile.  The statistics pass runs 65-256 rows as
+// eight waves of one or two row tiles, the votes pass as four waves of two or
+// four.
+template <int D, int TW, bool PAGED, bool WA, int PASS, int KT, int WV>
 __global__ void __launch_bounds__(WV * 64)
-    __attribute__((amdgpu_waves_per_eu(BF16 && WV == 8 && TW == 1 ? 6 : 1)))
 snapkv_pass_kernel(const SnapkvParams p) {
-  using SH = SkShape<D, BF16, KT, WV>;
+  using SH = SkShape<D, false, KT, WV>;
   constexpr int NB = SH::NB;
   __shared__ __attribute__((aligned(16))) unsigned char kt[2][KT * SH::KROW];
   __shared__ float red[2][WV][KT];  // PASS 1: per-wave key sums of two tiles
@@ -117,95 +228,7 @@ snapkv_pass_kernel(const SnapkvParams p) {
     }
   }
 
-  const unsigned char* kbase = static_cast<const unsigned char*>(p.k);
-  const int64_t head_off = static_cast<int64_t>(hk) * p.s_head;
-  const int32_t* ptab = PAGED ? p.page_table + static_cast<int64_t>(b) * p.max_pages : nullptr;
-  const int pmask = (1 << p.page_shift) - 1;
-
-  // Cooperative tile load: thread -> key row (threadIdx / LPT) + n * ROWS_PER_WG_LOAD,
-  // 16 B chunk threadIdx % LPT; a wave's lanes cover RPW consecutive rows of
-  // each load.  Page ids are read one tile ahead of the K loads that use
-  // them, so a tile's loads never wait on a page-table read.
-  //  WA (pages of at least RPW rows, or contiguous rows): a wave's RPW rows
-  //    lie in one page, so their base address is wave-uniform scalar
-  //    arithmetic and each lane adds a fixed 32-bit offset.  Rows past the
-  //    range read the range's last key (contiguous) or stay inside the page
-  //    of the group's first row; a group wholly past it reads element 0.
-  //  !WA: each lane computes its own row address; keys past the range read
-  //    element 0.  Keys past the range are masked either way.
-  constexpr int RPW = 64 / SH::LPT;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const uint32_t lane_chunk = static_cast<uint32_t>(lane % SH::LPT) * 16;
-  const uint32_t lane_row = static_cast<uint32_t>(lane / SH::LPT);
-  const uint32_t row_bytes = WA ? static_cast<uint32_t>(p.s_tok * SH::ES) : 0;
-  const uint32_t lane_off = lane_row * row_bytes + lane_chunk;
-
-  // Page ids of a tile's loads: per lane (pid[n], !WA), or, with WA, one
-  // vector read in which lane n < NLD fetches load n's id (pid[0]), taken
-  // out with readlane where the load is issued.
-  auto load_pids = [&](int (&pid)[SH::NLD], int tile) {
-    if constexpr (PAGED) {
-      if constexpr (WA) {
-        const int n = lane % SH::NLD;
-        const int jw = v_begin + tile * KT + n * SH::ROWS_PER_WG_LOAD + wave_u * RPW;
-        const bool ok = tile < n_tiles && jw < v_end;
-        const int pg = ptab[ok ? (jw >> p.page_shift) : 0];
-        pid[0] = ok ? pg : -1;
-      } else {
-        for (int n = 0; n < SH::NLD; ++n) {
-          const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
-          const int j = v_begin + tile * KT + tt;
-          const bool ok = tile < n_tiles && j < v_end;
-          pid[n] = ptab[ok ? (j >> p.page_shift) : 0];
-        }
-      }
-    }
-  };
-  auto load_tile = [&](sk_u32x4 (&x)[SH::NLD], int tile, const int (&pid)[SH::NLD]) {
-    if (tile >= n_tiles) return;  // past the chunk: nothing to stage
-    for (int n = 0; n < SH::NLD; ++n) {
-      int64_t off = 0;
-      uint32_t voff = lane_chunk;
-      if constexpr (WA) {
-        const int jw = v_begin + tile * KT + n * SH::ROWS_PER_WG_LOAD + wave_u * RPW;
-        voff = lane_off;
-        if constexpr (PAGED) {
-          const int pg = __builtin_amdgcn_readlane(pid[0], n);
-          const bool ok = pg >= 0 && pg < p.num_pages;
-          off = ok ? static_cast<int64_t>(pg) * p.s_blk +
-                         static_cast<int64_t>(jw & pmask) * p.s_tok + head_off
-                   : 0;
-          if (!ok) voff = lane_chunk;
-        } else {
-          const int jc = min(jw, v_end - 1);
-          off = static_cast<int64_t>(b) * p.s_blk + static_cast<int64_t>(jc) * p.s_tok + head_off;
-          if (jw + RPW > v_end)  // a group that reaches past the range
-            voff = min(lane_row, static_cast<uint32_t>(v_end - 1 - jc)) * row_bytes + lane_chunk;
-        }
-      } else {
-        const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
-        const int j = v_begin + tile * KT + tt;
-        bool ok = j < v_end;
-        if (PAGED) {
-          ok = ok && pid[n] >= 0 && pid[n] < p.num_pages;
-          off = ok ? static_cast<int64_t>(pid[n]) * p.s_blk +
-                         static_cast<int64_t>(j & pmask) * p.s_tok + head_off
-                   : 0;
-        } else {
-          off = ok ? static_cast<int64_t>(b) * p.s_blk + static_cast<int64_t>(j) * p.s_tok + head_off
-                   : 0;
-        }
-      }
-      x[n] = __builtin_nontemporal_load(
-          reinterpret_cast<const sk_u32x4*>(kbase + off * SH::ES + voff));
-    }
-  };
-  auto store_tile = [&](const sk_u32x4 (&x)[SH::NLD], int buf) {
-    for (int n = 0; n < SH::NLD; ++n) {
-      const int tt = n * SH::ROWS_PER_WG_LOAD + threadIdx.x / SH::LPT;
-      *reinterpret_cast<sk_u32x4*>(kt[buf] + tt * SH::KROW + (threadIdx.x % SH::LPT) * 16) = x[n];
-    }
-  };
+  SkLoader<D, false, PAGED, WA, KT, WV> ld(p, b, hk, v_begin, v_end, n_tiles, lane, wave);
 
   // Row statistics: the running max in the exponent's units (score x scale
   // x log2e, the scale folded into the exponent's fused multiply-add) and
@@ -220,9 +243,9 @@ snapkv_pass_kernel(const SnapkvParams p) {
 
   sk_u32x4 xr[SH::NLD];
   int pids[SH::NLD] = {};
-  load_pids(pids, 0);
-  load_tile(xr, 0, pids);
-  load_pids(pids, 1);
+  ld.load_pids(pids, 0);
+  ld.load_tile(xr, 0, pids);
+  ld.load_pids(pids, 1);
   const int n_full = n_tiles > 0 ? (v_end - v_begin) / KT : 0;  // tiles with every key in range
   // Tiles before n_plain hold only in-range keys that every observation
   // query sees (j < S - n_obs <= its position): no mask.  PASS 1 covers only
@@ -240,11 +263,11 @@ snapkv_pass_kernel(const SnapkvParams p) {
   };
   auto body = [&](int tile, auto masked) {
     const int buf = tile & 1;
-    store_tile(xr, buf);
+    ld.store_tile(xr, kt[buf]);
     __syncthreads();
     if (PASS == 1 && tile > 0) reduce_votes(tile - 1);
-    load_tile(xr, tile + 1, pids);  // next tile in flight while this one is used
-    load_pids(pids, tile + 2);
+    ld.load_tile(xr, tile + 1, pids);  // next tile in flight while this one is used
+    ld.load_pids(pids, tile + 2);
     const int v0 = v_begin + tile * KT;
 
     // S = Q K^T for this wave's row tiles and the tile's NB 16-key blocks.
@@ -255,15 +278,9 @@ snapkv_pass_kernel(const SnapkvParams p) {
       for (int cb = 0; cb < SH::KCB; ++cb) {
         const sk_u32x4 kk = *reinterpret_cast<const sk_u32x4*>(krow + cb * 64);
         for (int t = 0; t < TW; ++t) {
-          if constexpr (BF16) {
-            sacc[t][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(sk_bf16x8, qreg[t][cb]), __builtin_bit_cast(sk_bf16x8, kk),
-                sacc[t][tb], 0, 0, 0);
-          } else {
-            for (int jj = 0; jj < 4; ++jj)
-              sacc[t][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                  __uint_as_float(qreg[t][cb][jj]), __uint_as_float(kk[jj]), sacc[t][tb], 0, 0, 0);
-          }
+          for (int jj = 0; jj < 4; ++jj)
+            sacc[t][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                __uint_as_float(qreg[t][cb][jj]), __uint_as_float(kk[jj]), sacc[t][tb], 0, 0, 0);
         }
       }
     }
@@ -350,20 +367,303 @@ snapkv_pass_kernel(const SnapkvParams p) {
   }
 }
 
-// lse2[unit][r] = log2 sum over chunks of l_c * 2^(m_c).
-__global__ void __launch_bounds__(256) snapkv_lse_kernel(const SnapkvParams p) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(p.n_units) * p.R) return;
-  const int64_t unit = i / p.R, r = i % p.R;
-  float M = -INFINITY;
-  for (int c = 0; c < p.n_chunks; ++c) M = fmaxf(M, p.part_m[(unit * p.n_chunks + c) * p.R + r]);
-  float L = 0.f;
-  if (M != -INFINITY)
-    for (int c = 0; c < p.n_chunks; ++c) {
-      const float m = p.part_m[(unit * p.n_chunks + c) * p.R + r];
-      if (m != -INFINITY) L += p.part_l[(unit * p.n_chunks + c) * p.R + r] * __builtin_amdgcn_exp2f(m - M);
+// The bf16 passes.  Bounded by vector issue, not by HBM: per (row, key) score
+// the method costs a multiply-add, an exponential and an add, next to one
+// read of 2 d bytes per key.  So a wave owns a large block of scores per tile
+// (32 NR rows x 32 keys on v_mfma_f32_32x32x16_bf16) and the work around the
+// scores -- K staging, LDS reads, addresses, the barrier -- is paid once for
+// all of them.  RH row groups x KH key groups of waves share each tile of
+// 32 KH keys, so a K row is read from LDS by RH waves (16-row tiles with
+// every wave reading every key: by eight), and rows padded to an odd multiple
+// of 16 B leave the 32-row operand reads free of bank conflicts.
+//   PASS 0 computes S^T = K Q^T: a lane holds one query row per 32-row block
+//     and 16 of the tile's keys, so its running max and sum are two registers
+//     per block and the rescale is paid once per 16 keys.
+//   PASS 1 computes S = Q K^T: a lane holds one key and 16 rows per block, so
+//     a key's vote sums inside the lane.
+// Two tiles are in flight in registers; one barrier per tile, two LDS buffers.
+// Measured against passes of 16-row tiles (eight and four waves, 64-key
+// tiles, every wave reading every key, 44% and 32% of LDS cycles in
+// conflicts): 64 prompts of 32768 tokens, 128 rows, 1819 -> 1710 us; four
+// prompts of 5000-12000 tokens, 256 rows, 92 -> 67 us; 8 prompts of 8192, 32
+// rows, 65 -> 52 us.  On the full batch the load stream alone takes 680 us a
+// pass and the whole pass ~850: the clock drops under the matrix work (1.5 GHz
+// measured), so waves of two row blocks, which halve the LDS reads, or a third
+// of the workgroup's waves less change nothing (1720-1760 us).
+template <int D, int NR, int RH, int KH, bool PAGED, bool WA, int PASS>
+__global__ void __launch_bounds__(RH * KH * 64) __attribute__((amdgpu_waves_per_eu(2)))
+snapkv_pass_kernel_bf16(const SnapkvParams p) {
+  constexpr int P = 2;  // tiles in flight
+  constexpr int WV = RH * KH;
+  constexpr int KT = 32 * KH;
+  using SH = SkShape<D, true, KT, WV>;
+  constexpr int KS = D / 16;  // MFMA steps along the channels
+  __shared__ __attribute__((aligned(16))) unsigned char kt[2][KT * SH::KROW];
+  // PASS 1: per-row-group key sums of two tiles, and the votes of VT tiles,
+  // written out together.  PASS 0: per-key-group (max, sum) of each row.
+  constexpr int VT = kSkVoteBuf / KT;
+  __shared__ float red[2][RH][KT];
+  __shared__ __attribute__((aligned(16))) float vbuf[PASS == 1 ? kSkVoteBuf : 1];
+  __shared__ float fin[2][KH][PASS == 0 ? RH * NR * 32 : 1];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int l32 = lane & 31;
+  const int half = lane >> 5;
+  const int rh = wave % RH, kh = wave / RH;
+  // Chunk-major numbering, as in the attention kernel: workgroups that start
+  // together read the same key range of neighbouring kv heads (measured:
+  // equal to 1.8% faster than unit-major).
+  const int n_unit_grid = static_cast<int>(gridDim.x) / p.n_chunks;
+  const int chunk = static_cast<int>(blockIdx.x) / n_unit_grid;
+  const int unit = static_cast<int>(blockIdx.x) % n_unit_grid;
+  const int hk = unit % p.Hkv;
+  const int b = unit / p.Hkv;
+  const int S = min(max(p.kv_lens[b], 0), p.max_kv_len);
+  const int n_pre = max(S - p.n_obs, 0);
+  // PASS 0 covers every key a query sees; PASS 1 only the prefix that is voted on.
+  const int U = PASS == 0 ? S : n_pre;
+  const int v_begin = chunk * p.chunk_len;
+  const int v_end = min(U, v_begin + p.chunk_len);
+  const int n_tiles = v_end > v_begin ? (v_end - v_begin + KT - 1) / KT : 0;
+  const int row0 = rh * NR * 32;  // the wave's first row; r = o * G + g
+
+  SkLoader<D, true, PAGED, WA, KT, WV> ld(p, b, hk, v_begin, v_end, n_tiles, lane, wave);
+  sk_u32x4 x[P][SH::NLD];
+  int pids[P][SH::NLD] = {};
+#pragma unroll
+  for (int s = 0; s < P; ++s) ld.load_pids(pids[s], s);
+
+  // Q operand (A or B alike): lane (l32, half) of step ks holds channels
+  // ks * 16 + half * 8 .. + 7 of row l32 of each block.
+  sk_u32x4 qreg[NR][KS];
+#pragma unroll
+  for (int rb = 0; rb < NR; ++rb) {
+    const int r = row0 + rb * 32 + l32;
+    const bool ok = r < p.R;
+    const int o = ok ? r / p.G : 0, g = ok ? r % p.G : 0;
+    const unsigned char* qp = static_cast<const unsigned char*>(p.q) +
+                              ((static_cast<int64_t>(b) * p.n_obs + o) * p.Hq + hk * p.G + g) * D * 2;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      qreg[rb][ks] = *reinterpret_cast<const sk_u32x4*>(qp + ks * 32 + half * 16);
+      if (!ok) qreg[rb][ks] = sk_u32x4{0, 0, 0, 0};
     }
-  p.lse2[i] = L > 0.f ? M + __builtin_amdgcn_logf(L) : INFINITY;
+  }
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    ld.load_tile(x[s], s, pids[s]);
+    ld.load_pids(pids[s], s + P);
+  }
+
+  const float c2 = p.scale_log2;
+  // PASS 0: the lane's row of each block -- its position, and its running max
+  // (in the exponent's units: score x scale x log2e) and sum.
+  int row_pos[NR];
+  float mc_run[NR], l_run[NR];
+  // PASS 1: the log2-sum-exp of the lane's rows (+inf for padding: p = 0).
+  float lse2[NR][16];
+#pragma unroll
+  for (int rb = 0; rb < NR; ++rb) {
+    const int r = row0 + rb * 32 + l32;
+    row_pos[rb] = r < p.R ? S - p.n_obs + r / p.G : -1;
+    mc_run[rb] = -INFINITY;
+    l_run[rb] = 0.f;
+    if constexpr (PASS == 1) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int re = row0 + rb * 32 + (e & 3) + 8 * (e >> 2) + 4 * half;
+        lse2[rb][e] = re < p.R ? p.lse2[static_cast<int64_t>(unit) * p.R + re] : INFINITY;
+      }
+    }
+  }
+
+  const int n_full = n_tiles > 0 ? (v_end - v_begin) / KT : 0;  // tiles with every key in range
+  // Tiles before n_plain hold only in-range keys that every observation
+  // query sees (j < S - n_obs <= its position): no mask.  PASS 1 covers only
+  // such keys, up to its partial last tile.
+  const int n_plain = PASS == 0 ? min(n_full, max(n_pre - v_begin, 0) / KT) : n_tiles;
+  // PASS 1: add the row groups' sums of tile `tile` into the vote buffer.
+  auto reduce_votes = [&](int tile) {
+    if (static_cast<int>(threadIdx.x) < KT) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < RH; ++w) sum += red[tile & 1][w][threadIdx.x];
+      vbuf[(tile % VT) * KT + threadIdx.x] = sum;
+    }
+  };
+  // PASS 1: write the buffered votes of the tiles up to `tile`, whose buffer
+  // entries a barrier has made visible.
+  float* vout = p.votes + (static_cast<int64_t>(b) * p.Hkv + hk) * p.votes_stride + v_begin;
+  auto flush_votes = [&](int tile) {
+    const int t0 = tile / VT * VT;
+    for (int i = threadIdx.x; i < (tile - t0 + 1) * KT; i += WV * 64)
+      if (v_begin + t0 * KT + i < v_end) vout[t0 * KT + i] = vbuf[i];
+  };
+  auto body = [&](int tile, int buf, sk_u32x4 (&xs)[SH::NLD], int (&pid)[SH::NLD], auto masked) {
+    ld.store_tile(xs, kt[buf]);
+    ld.load_tile(xs, tile + P, pid);  // the slot's next tile, in flight while this one is used
+    ld.load_pids(pid, tile + 2 * P);
+    __syncthreads();
+    if constexpr (PASS == 1) {
+      // Tile t's sums were left before this barrier; entries reduced after the
+      // last one are visible now.
+      if (tile > 1 && (tile - 1) % VT == 0) flush_votes(tile - 2);
+      if (tile > 0) {
+        if ((tile - 1) % VT == 0) __syncthreads();  // the flush above is read before it is rewritten
+        reduce_votes(tile - 1);
+      }
+    }
+
+    sk_f32x16 acc[NR];
+#pragma unroll
+    for (int rb = 0; rb < NR; ++rb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[rb][e] = 0.f;
+    const unsigned char* krow = kt[buf] + (kh * 32 + l32) * SH::KROW + half * 16;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const sk_bf16x8 kk =
+          __builtin_bit_cast(sk_bf16x8, *reinterpret_cast<const sk_u32x4*>(krow + ks * 32));
+#pragma unroll
+      for (int rb = 0; rb < NR; ++rb) {
+        const sk_bf16x8 qq = __builtin_bit_cast(sk_bf16x8, qreg[rb][ks]);
+        acc[rb] = PASS == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk, qq, acc[rb], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qq, kk, acc[rb], 0, 0, 0);
+      }
+    }
+
+    if constexpr (PASS == 0) {
+#pragma unroll
+      for (int rb = 0; rb < NR; ++rb) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          if constexpr (decltype(masked)::value) {
+            const int j = v_begin + tile * KT + kh * 32 + (e & 3) + 8 * (e >> 2) + 4 * half;
+            if (!(j < v_end && j <= row_pos[rb])) acc[rb][e] = -INFINITY;
+          }
+          mx = fmaxf(mx, acc[rb][e]);
+        }
+        const float mcn = fmaxf(mc_run[rb], mx * c2);
+        // Unmasked tiles come first and give every row a finite max on the
+        // first of them; only masked tiles can meet a row with none (then the
+        // sums use 0 as reference and the max stays -inf).
+        float mcu = mcn;
+        if constexpr (decltype(masked)::value) mcu = mcn == -INFINITY ? 0.f : mcn;
+        float s0 = 0.f, s1 = 0.f;  // two chains of adds
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          s0 += __builtin_amdgcn_exp2f(fmaf(acc[rb][e], c2, -mcu));
+          s1 += __builtin_amdgcn_exp2f(fmaf(acc[rb][e + 1], c2, -mcu));
+        }
+        l_run[rb] = fmaf(l_run[rb], __builtin_amdgcn_exp2f(mc_run[rb] - mcu), s0 + s1);
+        mc_run[rb] = mcn;
+      }
+    } else {
+      // p = 2^(s*scale*log2e - lse2) summed over the lane's rows of its key,
+      // then over the two lane halves.
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int rb = 0; rb < NR; ++rb)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          s0 += __builtin_amdgcn_exp2f(fmaf(acc[rb][e], c2, -lse2[rb][e]));
+          s1 += __builtin_amdgcn_exp2f(fmaf(acc[rb][e + 1], c2, -lse2[rb][e + 1]));
+        }
+      float col = s0 + s1;
+      col += __shfl_xor(col, 32);
+      if (half == 0) red[buf][rh][kh * 32 + l32] = col;
+    }
+    // No barrier here: the next tile stages into the other buffer, and this
+    // buffer and these sums are rewritten only after the next tile's barrier,
+    // which every wave reaches after finishing this tile.
+  };
+  int tile = 0;
+  for (; tile + 2 <= n_plain; tile += 2) {
+    body(tile, 0, x[0], pids[0], std::false_type{});
+    body(tile + 1, 1, x[P - 1], pids[P - 1], std::false_type{});
+  }
+  for (; tile < n_tiles; tile += 2) {
+    body(tile, 0, x[0], pids[0], std::true_type{});
+    if (tile + 1 < n_tiles) body(tile + 1, 1, x[P - 1], pids[P - 1], std::true_type{});
+  }
+  if constexpr (PASS == 1) {
+    if (n_tiles > 0) {
+      __syncthreads();
+      if (n_tiles > 1 && (n_tiles - 1) % VT == 0) {
+        flush_votes(n_tiles - 2);
+        __syncthreads();
+      }
+      reduce_votes(n_tiles - 1);
+      __syncthreads();
+      flush_votes(n_tiles - 1);
+    }
+  } else {
+    // Combine each row over the two lane halves and the key groups, then
+    // write (m, l) for this chunk.
+#pragma unroll
+    for (int rb = 0; rb < NR; ++rb) {
+      float m = mc_run[rb], l = l_run[rb];
+      const float mo = __shfl_xor(m, 32), lo = __shfl_xor(l, 32);
+      const float mn = fmaxf(m, mo);
+      const float m_use = mn == -INFINITY ? 0.f : mn;
+      l = l * __builtin_amdgcn_exp2f(m - m_use) + lo * __builtin_amdgcn_exp2f(mo - m_use);
+      if (half == 0) {
+        fin[0][kh][row0 + rb * 32 + l32] = mn;
+        fin[1][kh][row0 + rb * 32 + l32] = l;
+      }
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r < p.R; r += WV * 64) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < KH; ++k) m = fmaxf(m, fin[0][k][r]);
+      const float m_use = m == -INFINITY ? 0.f : m;
+      float l = 0.f;
+#pragma unroll
+      for (int k = 0; k < KH; ++k) l += fin[1][k][r] * __builtin_amdgcn_exp2f(fin[0][k][r] - m_use);
+      const int64_t at = (static_cast<int64_t>(unit) * p.n_chunks + chunk) * p.R + r;
+      p.part_m[at] = m;
+      p.part_l[at] = l;
+    }
+  }
+}
+
+// lse2[unit][r] = log2 sum over chunks of l_c * 2^(m_c).  A workgroup takes 64
+// rows (one per lane, so the partials of a chunk are read coalesced); its
+// waves take the chunks in turn and merge through LDS (one thread walking all
+// the chunks of a row is a chain of loads: 60 us at 128 chunks).
+constexpr int kSkLseWaves = 16;
+__global__ void __launch_bounds__(64 * kSkLseWaves) snapkv_lse_kernel(const SnapkvParams p) {
+  __shared__ float sm[kSkLseWaves][64], sl[kSkLseWaves][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int n_waves = static_cast<int>(blockDim.x) >> 6;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+  const bool live = i < static_cast<int64_t>(p.n_units) * p.R;
+  const int64_t unit = live ? i / p.R : 0, r = live ? i % p.R : 0;
+  const int64_t at0 = unit * p.n_chunks * p.R + r;
+  float m = -INFINITY, l = 0.f;
+#pragma unroll 4
+  for (int c = w; c < p.n_chunks; c += n_waves) {
+    const float mc = p.part_m[at0 + static_cast<int64_t>(c) * p.R];
+    const float lc = p.part_l[at0 + static_cast<int64_t>(c) * p.R];
+    const float mn = fmaxf(m, mc);
+    const float ref = mn == -INFINITY ? 0.f : mn;  // no key seen yet: both sums are 0
+    l = l * __builtin_amdgcn_exp2f(m - ref) + lc * __builtin_amdgcn_exp2f(mc - ref);
+    m = mn;
+  }
+  sm[w][lane] = m;
+  sl[w][lane] = l;
+  __syncthreads();
+  if (w == 0 && live) {
+    float M = -INFINITY;
+    for (int x = 0; x < n_waves; ++x) M = fmaxf(M, sm[x][lane]);
+    const float ref = M == -INFINITY ? 0.f : M;
+    float L = 0.f;
+    for (int x = 0; x < n_waves; ++x) L += sl[x][lane] * __builtin_amdgcn_exp2f(sm[x][lane] - ref);
+    p.lse2[i] = L > 0.f ? M + __builtin_amdgcn_logf(L) : INFINITY;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -723,24 +1023,26 @@ __global__ void __launch_bounds__(kSelThreads) snapkv_select_kernel(const Snapkv
 // ---------------------------------------------------------------------------
 // Host-side dispatch.
 
-template <int D, bool BF16, int TW, int PASS>
-static hipError_t sk_launch_tw(const SnapkvParams& p, bool paged, int64_t blocks, hipStream_t s) {
-  // Wave-uniform row addresses where a wave's rows share a page and the
-  // lane offsets fit 32 bits.
+// Wave-uniform row addresses where a wave's rows share a page and the lane
+// offsets fit 32 bits.
+template <int D, bool BF16>
+static bool sk_wave_addresses(const SnapkvParams& p, bool paged) {
   using SH = SkShape<D, BF16>;
   constexpr int RPW = 64 / SH::LPT;
-  const bool wa = (!paged || (int64_t{1} << p.page_shift) >= RPW) &&
-                  p.s_tok >= 0 && p.s_tok * SH::ES * RPW <= (int64_t{1} << 30);
-#define MD_SK_LAUNCH(PG, WAV)                                                                 \
-  do {                                                                                        \
-    if constexpr (TW == 1 || PASS == 1)                                                       \
-      hipLaunchKernelGGL((snapkv_pass_kernel<D, BF16, TW, PG, WAV, PASS, kSkTile, kSkWaves>), \
-                         dim3(blocks), dim3(kSkWaves * 64), 0, s, p);                         \
-    else                                                                                      \
-      hipLaunchKernelGGL((snapkv_pass_kernel<D, BF16, TW / 2, PG, WAV, PASS, kSkTile,         \
-                                             kSkWavesWide>),                                  \
-                         dim3(blocks), dim3(kSkWavesWide * 64), 0, s, p);                     \
-  } while (0)
+  return (!paged || (int64_t{1} << p.page_shift) >= RPW) && p.s_tok >= 0 &&
+         p.s_tok * SH::ES * RPW <= (int64_t{1} << 30);
+}
+
+template <int D, int TW, int PASS>
+static hipError_t sk_launch_f32_tw(const SnapkvParams& p, bool paged, int64_t blocks,
+                                   hipStream_t s) {
+  constexpr int TWK = TW == 1 || PASS == 1 ? TW : TW / 2;
+  constexpr int WV = TW == 1 || PASS == 1 ? kSkWaves : kSkWavesWide;
+  const bool wa = sk_wave_addresses<D, false>(p, paged);
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(WV * 64);
+#define MD_SK_LAUNCH(PG, WAV)                                                                  \
+  hipLaunchKernelGGL((snapkv_pass_kernel<D, TWK, PG, WAV, PASS, kSkTile, WV>), grid, block, 0, \
+                     s, p)
   if (paged) {
     if (wa) MD_SK_LAUNCH(true, true); else MD_SK_LAUNCH(true, false);
   } else {
@@ -750,26 +1052,59 @@ static hipError_t sk_launch_tw(const SnapkvParams& p, bool paged, int64_t blocks
   return hipGetLastError();
 }
 
-template <int D, bool BF16, int PASS>
-static hipError_t sk_launch_d(const SnapkvParams& p, int TW, bool paged, int64_t blocks,
-                              hipStream_t s) {
+template <int D, int PASS>
+static hipError_t sk_launch_f32(const SnapkvParams& p, int TW, bool paged, int64_t blocks,
+                                hipStream_t s) {
   switch (TW) {
-    case 1: return sk_launch_tw<D, BF16, 1, PASS>(p, paged, blocks, s);
-    case 2: return sk_launch_tw<D, BF16, 2, PASS>(p, paged, blocks, s);
-    case 4: return sk_launch_tw<D, BF16, 4, PASS>(p, paged, blocks, s);
+    case 1: return sk_launch_f32_tw<D, 1, PASS>(p, paged, blocks, s);
+    case 2: return sk_launch_f32_tw<D, 2, PASS>(p, paged, blocks, s);
+    case 4: return sk_launch_f32_tw<D, 4, PASS>(p, paged, blocks, s);
   }
   return hipErrorInvalidValue;
+}
+
+template <int D, int NR, int RH, int KH, int PASS>
+static hipError_t sk_launch_grid(const SnapkvParams& p, bool paged, int64_t blocks,
+                                 hipStream_t s) {
+  const bool wa = sk_wave_addresses<D, true>(p, paged);
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(RH * KH * 64);
+#define MD_SK_LAUNCH(PG, WAV)                                                                 \
+  hipLaunchKernelGGL((snapkv_pass_kernel_bf16<D, NR, RH, KH, PG, WAV, PASS>), grid, block, 0, \
+                     s, p)
+  if (paged) {
+    if (wa) MD_SK_LAUNCH(true, true); else MD_SK_LAUNCH(true, false);
+  } else {
+    if (wa) MD_SK_LAUNCH(false, true); else MD_SK_LAUNCH(false, false);
+  }
+#undef MD_SK_LAUNCH
+  return hipGetLastError();
+}
+
+// The wave grid by rows.  One 32-row block per wave and 32-key tiles, the
+// smallest workgroups, wait least on each other at the tile's barrier (full
+// batch, 128 rows: 1700 us against 1736 with 64-key tiles and eight waves, and
+// 1735 with two blocks a wave and 64 keys).  256 rows of d = 64 take two
+// blocks in four waves, since a 32-key tile is too small to load by eight.
+// Up to 32 rows two key groups share the tile, so that a workgroup keeps two
+// waves (50.5 us against 54.5 with four on 8 prompts of 8192).
+template <int D, int PASS>
+static hipError_t sk_launch_bf16(const SnapkvParams& p, bool paged, int64_t blocks, hipStream_t s) {
+  if (p.R <= 32) return sk_launch_grid<D, 1, 1, 2, PASS>(p, paged, blocks, s);
+  if (p.R <= 64) return sk_launch_grid<D, 1, 2, 1, PASS>(p, paged, blocks, s);
+  if (p.R <= 128) return sk_launch_grid<D, 1, 4, 1, PASS>(p, paged, blocks, s);
+  if constexpr (D == 128) return sk_launch_grid<D, 1, 8, 1, PASS>(p, paged, blocks, s);
+  return sk_launch_grid<D, 2, 4, 1, PASS>(p, paged, blocks, s);
 }
 
 template <int PASS>
 static hipError_t sk_launch(const SnapkvParams& p, int head_dim, bool bf16, int TW, bool paged,
                             int64_t blocks, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
-  if (head_dim == 128)
-    return bf16 ? sk_launch_d<128, true, PASS>(p, TW, paged, blocks, s)
-                : sk_launch_d<128, false, PASS>(p, TW, paged, blocks, s);
-  return bf16 ? sk_launch_d<64, true, PASS>(p, TW, paged, blocks, s)
-              : sk_launch_d<64, false, PASS>(p, TW, paged, blocks, s);
+  if (bf16)
+    return head_dim == 128 ? sk_launch_bf16<128, PASS>(p, paged, blocks, s)
+                           : sk_launch_bf16<64, PASS>(p, paged, blocks, s);
+  return head_dim == 128 ? sk_launch_f32<128, PASS>(p, TW, paged, blocks, s)
+                         : sk_launch_f32<64, PASS>(p, TW, paged, blocks, s);
 }
 
 hipError_t launch_snapkv_votes(const SnapkvParams& p, int head_dim, bool bf16, int TW, bool paged,
@@ -781,8 +1116,8 @@ hipError_t launch_snapkv_votes(const SnapkvParams& p, int head_dim, bool bf16, i
                               static_cast<int64_t>(p.n_units) * q.n_chunks, s);
   if (e != hipSuccess) return e;
   const int64_t rows = static_cast<int64_t>(p.n_units) * p.R;
-  hipLaunchKernelGGL(snapkv_lse_kernel, dim3(static_cast<uint32_t>((rows + 255) / 256)), dim3(256),
-                     0, s, q);
+  hipLaunchKernelGGL(snapkv_lse_kernel, dim3(static_cast<uint32_t>((rows + 63) / 64)),
+                     dim3(64 * std::min(q.n_chunks, kSkLseWaves)), 0, s, q);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   q.chunk_len = p.chunk_len_votes;

@@ -91,6 +91,22 @@ def test_votes_random(seed):
     test_votes_against_oracle(_random_votes_case(seed))
 
 
+# (G, n_obs, d): rows at and past each wave grid of the bf16 passes (32, 64, 128, 256 rows).
+GRID_ROWS = [(1, 32, 128), (3, 11, 128), (2, 32, 64), (5, 13, 128), (4, 32, 128), (3, 43, 64),
+             (8, 32, 128), (8, 32, 64), (1, 1, 64)]
+
+
+@pytest.mark.parametrize("G,n_obs,d", GRID_ROWS)
+def test_votes_wave_grids(G, n_obs, d):
+    """Prefixes at the edges of a tile (32, 64 keys), of the vote buffer (1024)
+    and of several chunks, in pages and contiguous, within the bound of
+    test_votes_against_oracle."""
+    for ps, pre in ((16, [0, 31, 33]), (0, [64, 1023, 1025]), (2, [1, 2500]), (16, [128 * 40 + 1])):
+        lens = [n + n_obs for n in pre]
+        test_votes_against_oracle((f"grid_g{G}_o{n_obs}_d{d}_p{ps}", len(lens), n_obs, 2 * G, 2, d,
+                                   lens, "bf16", ps))
+
+
 # rows, stride, n_obs, budget, pool, prompt lens (per sequence), Hkv
 SELECT = [
     (3, 500, 32, 64, 5, [532, 300, 40], 2),

@@ -129,8 +129,14 @@ int64_t grid_size(const Plan& pl, int lpt) {
 }  // namespace
 
 int64_t attn_grid_size(const md_attn_args* a, int mode, int n_sink, int window) {
-  const Plan pl = make_plan(a, mode, n_sink, window, device_cu_count());
+  const Plan pl = plan_call(a, mode, n_sink, window, device_cu_count());
   return grid_size(pl, !pl.bal && longest_first(mode, pl.n_chunks, a->num_seqs, a->max_kv_len));
+}
+
+bool attn_runs_unsplit(const md_attn_args* a, int mode, int n_sink, int window) {
+  if (check_attn_sizes(a) != MD_OK) return false;
+  if (mode == MD_MODE_DRAFT && (n_sink < 0 || window < 1 || window > kMaxPosition)) return false;
+  return plan_call(a, mode, n_sink, window, device_cu_count()).workspace_bytes == 0;
 }
 
 // The attention entry points.  `workspace`/`workspace_bytes` override the
@@ -156,7 +162,7 @@ int run_attention(const md_attn_args* a, int mode, int n_sink, int window, void*
       return MD_ERR_INVALID_ARG;
   }
   const int num_cus = device_cu_count();
-  const Plan pl = make_plan(a, mode, n_sink, window, num_cus);
+  const Plan pl = plan_call(a, mode, n_sink, window, num_cus);
   const bool bf16 = a->dtype == MD_BF16;
   const bool paged = a->page_size != 0;
 

@@ -27,7 +27,12 @@ constexpr int kWaves = 4;
 // Waves of the wide instances (up to two row tiles of bf16): two per SIMD.
 constexpr int kWavesWide = 8;
 constexpr int kTile = 32;            // tokens per wave iteration
-constexpr int kMinChunkTokens = 1024;  // every wave gets >= 8 tiles of a chunk
+constexpr int kMinChunkTokens = 128;  // shortest chunk of a split range: a tile per wave
+constexpr int64_t kWholeTokens = 256;  // ranges up to this are not split
+constexpr int64_t kWholeList = 1020;   // listed drafts: lists up to this are not split
+// Ranges up to this are split only for a caller that gives a workspace: they
+// fit one pass, so a call without one runs unsplit instead of being refused.
+constexpr int64_t kSplitNeedsWorkspace = 1024;
 constexpr int kMaxRows = 64;         // G*L bound: at most four 16-row tiles
 constexpr int kPairMinChunkTokens = 4096;  // head pairs on split ranges: chunks at least this long
 constexpr int kMaxChunks = 65535;    // a split plan's arrival count fits 16 bits
@@ -95,7 +100,14 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window);
 // The decomposition for these sizes on a device with num_cus compute units.
 // Only sizes are read from `a`.  Call after validate_attn succeeded.
 // mode MD_MODE_DRAFT_INDEXED reads `window` as the list capacity idx_stride.
-Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus);
+// Ranges of at most `whole` tokens are not split.
+Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus,
+               int64_t whole = 0);
+
+// The decomposition a call runs: make_plan, or its unsplit form when the range
+// fits one pass (kSplitNeedsWorkspace) and the caller's workspace does not
+// serve the split.
+Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus);
 
 // SnapKV selection: validation and the chunking of its two passes.
 constexpr int kSnapkvMaxRows = 256;  // G * n_obs
@@ -144,6 +156,10 @@ int run_attention(const md_attn_args* a, int mode, int n_sink, int window, void*
 
 // Workgroups the attention launch for these (validated) arguments uses.
 int64_t attn_grid_size(const md_attn_args* a, int mode, int n_sink, int window);
+
+// Whether this call, with the workspace in `a`, runs as a single pass (false
+// for malformed sizes, which the call itself reports).
+bool attn_runs_unsplit(const md_attn_args* a, int mode, int n_sink, int window);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

@@ -73,6 +73,12 @@ extern "C" int md_attn_noalloc(const md_attn_args* a, int32_t mode, int32_t n_si
   }
   void* ws = md::scratch_address(dev, &e);
   if (!ws) return md::hip_fail(e);
-  return md::run_attention(a, mode, n_sink, window, stream, nullptr, nullptr, ws,
+  // A range that fits one pass is not split here: such calls leave the shared
+  // scratch alone, so they may overlap.
+  md_attn_args local = *a;
+  local.workspace = nullptr;
+  local.workspace_bytes = 0;
+  if (md::attn_runs_unsplit(&local, mode, n_sink, window)) ws = nullptr;
+  return md::run_attention(&local, mode, n_sink, window, stream, nullptr, nullptr, ws,
                            MD_NOALLOC_SCRATCH_BYTES, nullptr);
 }

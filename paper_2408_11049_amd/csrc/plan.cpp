@@ -86,7 +86,7 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window) {
   if (sizes != MD_OK) return sizes;
   if (a->num_seqs == 0) return MD_OK;  // nothing will be read or written
   const int num_cus = device_cu_count();
-  Plan p = make_plan(a, mode, n_sink, window, num_cus);
+  const Plan p = plan_call(a, mode, n_sink, window, num_cus);
   if (p.n_chunks > kMaxChunks) return MD_ERR_UNSUPPORTED;  // unreachable below ~16k compute units
 
   if (!a->q || !a->k || !a->v || !a->o || !a->kv_lens) return MD_ERR_INVALID_ARG;
@@ -114,15 +114,16 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window) {
 
 // The range split for n_groups workgroups' worth of units: one chunk each
 // when they alone cover every compute unit, else each range is cut just until
-// they do, never below kMinChunkTokens tokens per chunk.
-static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t* n_chunks_out,
-                        int64_t* chunk_len_out) {
+// they do, never below kMinChunkTokens tokens per chunk (a tile for each wave:
+// on MI355X a 5-token verify of one 4001-token sequence takes 27.7 us in
+// 1024-token chunks, 16.2 in 256 and 15.0 in 128).  A range of at most `whole`
+// tokens is not cut.
+static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whole,
+                        int64_t* n_chunks_out, int64_t* chunk_len_out) {
   int64_t n_chunks = 1;
   if (n_groups > 0 && n_groups < slots) {
-    n_chunks = ceil_div(slots, n_groups);
-    const int64_t cap = ceil_div(U, kMinChunkTokens);
-    if (n_chunks > cap) n_chunks = cap;
-    if (n_chunks < 1) n_chunks = 1;
+    const int64_t cap = U <= whole ? 1 : ceil_div(U, kMinChunkTokens);
+    n_chunks = std::min(ceil_div(slots, n_groups), cap);
   }
   int64_t chunk_len = ceil_div(ceil_div(U, n_chunks), kTile) * kTile;
   if (chunk_len < kTile) chunk_len = kTile;
@@ -147,7 +148,8 @@ static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t* n_c
 // are taken in those two cases only.  A listed draft reads a different list
 // per head -- no adjacent rows -- and keeps one head per workgroup.
 // MD_HEADS_PER_WG (1 or 2) overrides, for measurement.
-static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64_t slots) {
+static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64_t slots,
+                               int64_t whole) {
   const int forced = env_knob("MD_HEADS_PER_WG", 1, 2);
   if (a->num_kv_heads % 2) return 1;
   if (forced) return forced;
@@ -155,11 +157,12 @@ static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64
   const int64_t pairs = static_cast<int64_t>(a->num_seqs) * a->num_kv_heads / 2;
   if (pairs >= slots) return 2;
   int64_t n_chunks, chunk_len;
-  split_units(U, pairs, slots, &n_chunks, &chunk_len);
+  split_units(U, pairs, slots, whole, &n_chunks, &chunk_len);
   return chunk_len >= kPairMinChunkTokens ? 2 : 1;
 }
 
-Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus) {
+Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus,
+               int64_t whole) {
   Plan p;
   const int L = a->q_len;
   p.G = a->num_q_heads / a->num_kv_heads;
@@ -173,7 +176,7 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // One workgroup of kWaves waves (one per SIMD) per compute unit is enough
   // to stream at full rate.  When the workgroups alone cover every compute
   // unit, one chunk per unit avoids the merge pass; else each unit's range is
-  // split just until they do, never below kMinChunkTokens tokens per chunk.  (Every
+  // split just until they do (split_units).  (Every
   // chunk pays a pipeline fill, a cross-wave merge and a partial write:
   // measured on MI355X, splitting further -- two or four workgroups per
   // compute unit -- was 5-15% slower on long caches and slower still on
@@ -181,10 +184,14 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // MD_SLOTS_SCALE = 2..4 plans for that many workgroups per compute unit
   // (measurement only).
   const int64_t slots = (num_cus > 0 ? num_cus : 256) * std::max(1, env_knob("MD_SLOTS_SCALE", 2, 4));
-  p.hp = heads_per_workgroup(a, mode, U, slots);
+  // 256 tokens in one chunk take 8.9-10.2 us and in two 9.4-11.0 (the merge
+  // costs more than the second tile).  A listed draft keeps lists of up to
+  // kWholeList positions whole, so that they need no workspace.
+  whole = std::max(whole, mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
+  p.hp = heads_per_workgroup(a, mode, U, slots, whole);
   p.n_groups = p.n_units / p.hp;
   int64_t n_chunks, chunk_len;
-  split_units(U, p.n_groups, slots, &n_chunks, &chunk_len);
+  split_units(U, p.n_groups, slots, whole, &n_chunks, &chunk_len);
   p.n_chunks = static_cast<int32_t>(n_chunks);
   p.chunk_len = static_cast<int32_t>(chunk_len);
   // Balanced verify: where the units alone fill the device and lengths may
@@ -237,25 +244,36 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   return p;
 }
 
+Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus) {
+  const Plan p = make_plan(a, mode, n_sink, window, num_cus);
+  if (p.n_chunks > 1 && p.U_max <= kSplitNeedsWorkspace &&
+      (!a->workspace || a->workspace_bytes < p.workspace_bytes ||
+       (reinterpret_cast<uintptr_t>(a->workspace) & 255u)))
+    return make_plan(a, mode, n_sink, window, num_cus, kSplitNeedsWorkspace);
+  return p;
+}
+
 namespace {
 
-// Chunks of a range of U keys over n_units units.  A few units are cut until
-// `fill` workgroups (what the device holds at once, about two rounds of it)
-// share the work, down to kSnapkvMinChunk keys: below that the prologue of a
+// Chunks of a range of U keys over n_units units.  A few units are cut into
+// at most `fill` workgroups (what the device holds at once; one more than fits
+// starts a second round: 50 fp32 units of 256 rows, 258 us in 250 workgroups and
+// 416 in 300), down to kSnapkvMinChunk keys: below that the prologue of a
 // chunk costs more than its keys (one prompt of 4000 tokens, 8 heads of 128
 // rows: 49 us at 1024 keys a chunk, 19.4 at 256, 15.2 at 128, 16.2 at 64).
-// Many long units are cut further, to sixteen workgroups per compute unit, so
-// that ragged lengths and the last round of workgroups even out, while a chunk
-// keeps kSnapkvLongChunk keys (64 prompts of 32768: 1700 us against 1764 with
+// Long units are cut further, into whole rounds of `fill` up to sixteen
+// workgroups per compute unit, so that ragged lengths even out, while a chunk
+// keeps about kSnapkvLongChunk keys (64 prompts of 32768: 1700 us against 1764 with
 // two chunks a unit; 16 prompts of 16384, 64 rows: 185 us at 2048 keys a chunk
 // and 197 at 1024).
 void split_range(int64_t U, int64_t n_units, int64_t fill, int num_cus, int32_t* n_chunks_out,
                  int32_t* chunk_len_out) {
   int64_t n_chunks = 1;
   if (n_units > 0) {
-    const int64_t few = std::min(ceil_div(fill, n_units), ceil_div(U, kSnapkvMinChunk));
-    const int64_t many = std::min(ceil_div(16 * int64_t{num_cus}, n_units), U / kSnapkvLongChunk);
-    n_chunks = std::max<int64_t>(1, std::max(few, many));
+    n_chunks = std::max<int64_t>(1, std::min(fill / n_units, ceil_div(U, kSnapkvMinChunk)));
+    const int64_t longest = ceil_div(U, kSnapkvLongChunk);
+    for (int64_t total = fill; total <= 16 * int64_t{num_cus}; total += fill)
+      if (total / n_units <= longest) n_chunks = std::max(n_chunks, total / n_units);
   }
   int64_t chunk_len = ceil_div(ceil_div(U > 0 ? U : 1, n_chunks), kTile) * kTile;
   n_chunks = ceil_div(U > 0 ? U : 1, chunk_len);

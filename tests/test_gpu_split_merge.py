@@ -112,3 +112,48 @@ def test_fused_matches_separate_merge(monkeypatch):
     d = float(np.max(np.abs(fused[0] - sep[0])))
     say(f"  fused vs separate: max|dO| = {d:.3e}")
     assert d <= TOL["bf16"] / 4
+
+
+# Ranges at the edges of the split (256 tokens stay whole; chunks of 128) and
+# merges of 2 to 126 parts: Hkv, Hq, L, lens, d, dtype.
+EDGES = [(1, 4, 4, [255], 64, "f32"), (1, 4, 4, [256], 128, "bf16"), (1, 4, 4, [257], 128, "bf16"),
+         (2, 8, 5, [1025, 300], 64, "bf16"), (1, 4, 1, [9 * 128], 128, "bf16"),
+         (1, 8, 5, [32 * 128, 5], 128, "bf16"), (1, 4, 2, [33 * 128 - 1], 64, "f32"),
+         (1, 2, 3, [16001], 128, "f32"), (1, 4, 1, [16100, 1, 700], 128, "bf16")]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[f"edge{i}" for i in range(len(EDGES))])
+@pytest.mark.parametrize("mode", ["verify", "draft"])
+def test_split_edges(case, mode):
+    """Short chunks and many-part merges against the oracle (drafts: the same
+    range as 3 sinks and a window)."""
+    Hkv, Hq, L, lens, d, dtype = case
+    lens = [max(n, L) for n in lens]
+    c = wl.make_case(B=len(lens), q_len=L, Hq=Hq, Hkv=Hkv, d=d, kv_lens=lens, dtype=dtype,
+                     page_size=16, seed=700 + max(lens) % 97, device=DEV)
+    m, s, w = (oracle.VERIFY, 0, 1) if mode == "verify" else \
+        (oracle.DRAFT, 3, max(1, max(lens) - 3 - (L - 1)))
+    say(f"[split-edge] {mode} {case}")
+    compare(*_call(m, c, None, s, w), *run_oracle(m, c, s, w), dtype, f"{mode} {case}")
+
+
+def test_short_ranges_without_a_workspace():
+    """A range of at most 1024 tokens splits when a workspace is given and runs
+    unsplit without one, or with one that is too small; both match the oracle."""
+    import ctypes
+    lib = md.load_library()
+    c = _case(1, 4, 8, 2, [1000], 16, 731)
+    need = _need(oracle.VERIFY, c)
+    assert need > 0
+    ref = run_oracle(oracle.VERIFY, c)
+    for nbytes in (None, 256, need):
+        ws = None if nbytes is None else torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        out = torch.full_like(c["q"], float("nan"))
+        lse = torch.full(c["q"].shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+        a = md.make_args(c["q"], c["k"], c["v"], c["kv_lens"], max_kv_len=c["max_kv_len"],
+                         page_table=c["page_table"], out=out, lse=lse, workspace=ws)
+        st = torch.cuda.current_stream().cuda_stream
+        assert lib.md_verify_attn(ctypes.byref(a), st) == md.MD_OK
+        torch.cuda.synchronize()
+        compare(out.float().cpu().numpy().astype(np.float64),
+                lse.cpu().numpy().astype(np.float64), *ref, "bf16", f"workspace {nbytes}")

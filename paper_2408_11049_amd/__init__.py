@@ -208,8 +208,13 @@ def _stream_scoped(fn):
 
 
 def _stream_handle(t, stream):
-    import torch
+    """The HIP stream of a call on t's device: `stream`, else the current one
+    (read without building a Stream object where torch offers that)."""
     if stream is None:
+        torch = _torch()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return ctypes.c_void_p(raw(t.get_device()))
         stream = torch.cuda.current_stream(t.device)
     return ctypes.c_void_p(stream.cuda_stream)
 
@@ -231,18 +236,26 @@ def _on_gpu(ref, **tensors):
 
 def _ints(name, t, n):
     """A device int32 vector the kernels read (or write) n entries of."""
-    import torch
+    torch = _torch()
     if t.dtype != torch.int32 or not t.is_contiguous() or t.numel() < n:
         raise ValueError(f"{name} must be contiguous int32 with at least {n} entries")
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    """The torch module, looked up once (an import statement per call costs as
+    much as several tensor attribute reads)."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t):
-    import torch
+    torch = _torch()
     if t.dtype == torch.float32:
         return MD_F32
     if t.dtype == torch.bfloat16:
@@ -254,61 +267,65 @@ def make_args(q, k, v, kv_lens, *, max_kv_len: Optional[int] = None, page_table=
               sm_scale: float = 0.0, out=None, lse=None, workspace=None,
               err_word=None) -> MdAttnArgs:
     """Fill md_attn_args from tensors (no data is read or moved)."""
-    if q.dim() != 4 or k.dim() != 4 or v.dim() != 4:
+    torch = _torch()
+    qs, ks = q.shape, k.shape
+    if len(qs) != 4 or len(ks) != 4 or v.dim() != 4:
         raise ValueError("q, k, v must be 4-D")
-    B, L, Hq, d = q.shape
+    B, L, Hq, d = qs
     paged = page_table is not None
-    _on_gpu(q, k=k, v=v, kv_lens=kv_lens, page_table=page_table, out=out, lse=lse,
-            workspace=workspace, err_word=err_word)
-    if k.shape != v.shape or k.stride() != v.stride():
+    gpu = q.get_device()
+    for t in (k, v, kv_lens, page_table, out, lse, workspace, err_word):
+        if gpu < 0 or (t is not None and t.get_device() != gpu):  # names the tensor and raises
+            _on_gpu(q, k=k, v=v, kv_lens=kv_lens, page_table=page_table, out=out, lse=lse,
+                    workspace=workspace, err_word=err_word)
+    kst = k.stride()
+    if ks != v.shape or kst != v.stride():
         raise ValueError("k and v must share shape and strides")
-    if k.shape[3] != d:
+    if ks[3] != d:
         raise ValueError("k/v head_dim must equal q's")
     _ints("kv_lens", kv_lens, B)
-    if out is not None and (out.shape != q.shape or out.dtype != q.dtype):
+    if out is not None and (out.shape != qs or out.dtype != q.dtype):
         raise ValueError("o must have q's shape and dtype")
-    if lse is not None and (lse.dtype != _torch().float32 or not lse.is_contiguous()
+    if lse is not None and (lse.dtype != torch.float32 or not lse.is_contiguous()
                             or lse.numel() < B * L * Hq):
         raise ValueError("lse must be contiguous float32 [B, L, Hq]")
     if paged and page_table.dim() == 2 and page_table.shape[0] < B:
         raise ValueError("page_table must have a row per sequence")
-    if k.stride(3) != 1:
+    if kst[3] != 1:
         raise ValueError("the head_dim axis of k/v must be unit-stride")
     if not q.is_contiguous() or (out is not None and not out.is_contiguous()):
         raise ValueError("q and o must be contiguous [B, L, Hq, d]")
     if max_kv_len is None:  # a bound that needs no device sync
-        max_kv_len = page_table.shape[1] * k.shape[1] if paged else k.shape[1]
-    if B > 0 and not paged and k.shape[1] < max_kv_len:
+        max_kv_len = page_table.shape[1] * ks[1] if paged else ks[1]
+    if B > 0 and not paged and ks[1] < max_kv_len:
         raise ValueError("contiguous k/v must hold max_kv_len tokens per sequence")
-    if B > 0 and not paged and k.shape[0] < B:
+    if B > 0 and not paged and ks[0] < B:
         raise ValueError("contiguous k/v must hold B sequences")
-    a = MdAttnArgs()
-    a.num_seqs, a.q_len, a.num_q_heads, a.num_kv_heads, a.head_dim = B, L, Hq, k.shape[2], d
-    a.dtype = _dtype_code(q)
-    if _dtype_code(k) != a.dtype or _dtype_code(v) != a.dtype:
+    dtype = _dtype_code(q)
+    if ((k.dtype != q.dtype or v.dtype != q.dtype) and
+            (_dtype_code(k) != dtype or _dtype_code(v) != dtype)):
         raise ValueError("q, k, v must share a dtype")
-    a.sm_scale = float(sm_scale)
-    a.q, a.k, a.v = q.data_ptr(), k.data_ptr(), v.data_ptr()
-    a.kv_stride_blk, a.kv_stride_tok, a.kv_stride_head = k.stride(0), k.stride(1), k.stride(2)
+    page_size = max_pages = num_pages = 0
+    pt = None
     if paged:
-        import torch
         if page_table.dtype != torch.int32 or not page_table.is_contiguous():
             raise ValueError("page_table must be contiguous int32 [B, max_pages]")
-        a.page_size, a.max_pages_per_seq = k.shape[1], page_table.shape[1]
-        a.num_pages = k.shape[0]
-        a.page_table = page_table.data_ptr()
-    a.kv_lens = kv_lens.data_ptr()
-    a.max_kv_len = int(max_kv_len)
-    a.o = out.data_ptr() if out is not None else None
-    a.lse = lse.data_ptr() if lse is not None else None
+        page_size, max_pages, num_pages = ks[1], page_table.shape[1], ks[0]
+        pt = page_table.data_ptr()
+    ws, ws_bytes = None, 0
     if workspace is not None:
-        a.workspace, a.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+        ws, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    err = None
     if err_word is not None:
-        import torch
         if err_word.dtype != torch.int32 or err_word.numel() < 1:
             raise ValueError("err_word must be a device int32 tensor")
-        a.err_word = err_word.data_ptr()
-    return a
+        err = err_word.data_ptr()
+    # in the order of MdAttnArgs._fields_
+    return MdAttnArgs(B, L, Hq, ks[2], d, dtype, float(sm_scale), q.data_ptr(), k.data_ptr(),
+                      v.data_ptr(), kst[0], kst[1], kst[2], page_size, max_pages, num_pages, pt,
+                      kv_lens.data_ptr(), int(max_kv_len),
+                      None if out is None else out.data_ptr(),
+                      None if lse is None else lse.data_ptr(), ws, ws_bytes, err)
 
 
 def md_workspace_bytes(q, k, v, kv_lens, *, mode=MD_MODE_VERIFY, n_sink=0, window=1, **kw) -> int:
@@ -321,36 +338,41 @@ def md_workspace_bytes(q, k, v, kv_lens, *, mode=MD_MODE_VERIFY, n_sink=0, windo
 def _attention(mode, q, k, v, kv_lens, n_sink, window, *, max_kv_len=None, page_table=None,
                sm_scale=0.0, out=None, lse=None, return_lse=True, workspace=None, stream=None,
                idx=None, idx_len=None, err_word=None):
-    import torch
+    torch = _torch()
     lib = load_library()
     if kv_lens.dtype != torch.int32:
         raise ValueError("kv_lens must be int32")
     if out is None:
         out = torch.empty_like(q)
     if lse is None and return_lse:
-        lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
+        lse = q.new_empty(q.shape[:3], dtype=torch.float32)
     a = make_args(q, k, v, kv_lens, max_kv_len=max_kv_len, page_table=page_table,
                   sm_scale=sm_scale, out=out, lse=lse, err_word=err_word)
-    if mode == MD_MODE_DRAFT_INDEXED:
-        need = int(lib.md_workspace_bytes_indexed(ctypes.byref(a), idx.shape[2]))
-    else:
-        need = int(lib.md_workspace_bytes(ctypes.byref(a), mode, n_sink, window))
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    _on_gpu(q, workspace=workspace, idx=idx, idx_len=idx_len)
+    ref = ctypes.byref(a)
+    if workspace is not None or idx is not None:
+        _on_gpu(q, workspace=workspace, idx=idx, idx_len=idx_len)
     if idx_len is not None:
         _ints("idx_len", idx_len, q.shape[0])
-    if workspace is not None:
+    if workspace is None:
+        if mode == MD_MODE_DRAFT_INDEXED:
+            need = lib.md_workspace_bytes_indexed(ref, idx.shape[2])
+        else:
+            need = lib.md_workspace_bytes(ref, mode, n_sink, window)
+        if need:
+            workspace = q.new_empty((need,), dtype=torch.uint8)
+            a.workspace, a.workspace_bytes = workspace.data_ptr(), need
+    else:
         a.workspace = workspace.data_ptr()
         a.workspace_bytes = workspace.numel() * workspace.element_size()
     s = _stream_handle(q, stream)
     if mode == MD_MODE_VERIFY:
-        st = lib.md_verify_attn(ctypes.byref(a), s)
+        st = lib.md_verify_attn(ref, s)
     elif mode == MD_MODE_DRAFT:
-        st = lib.md_draft_attn(ctypes.byref(a), int(n_sink), int(window), s)
+        st = lib.md_draft_attn(ref, int(n_sink), int(window), s)
     else:
-        st = lib.md_draft_attn_indexed(ctypes.byref(a), _ptr(idx), _ptr(idx_len), idx.shape[2], s)
-    _check(st)
+        st = lib.md_draft_attn_indexed(ref, _ptr(idx), _ptr(idx_len), idx.shape[2], s)
+    if st != MD_OK:
+        _check(st)
     return out, lse
 
 
@@ -390,7 +412,7 @@ def md_draft_attn_indexed(q, k, v, kv_lens, idx, idx_len, **kw):
 
     idx [B, Hkv, stride] int32 prompt positions (unique), idx_len [B] int32
     (see include/magicdec.h)."""
-    import torch
+    torch = _torch()
     if idx.dtype != torch.int32 or idx_len.dtype != torch.int32:
         raise ValueError("idx and idx_len must be int32")
     if idx.dim() != 3 or not idx.is_contiguous() or idx.shape[:2] != (q.shape[0], k.shape[2]):
@@ -431,7 +453,7 @@ def make_snapkv_args(q_obs, k, prompt_lens, *, max_prompt_len=None, page_table=N
                      sm_scale=0.0, votes=None, workspace=None) -> MdSnapkvArgs:
     """Fill md_snapkv_args from tensors (no data is read or moved); votes may
     be None to size the workspace only."""
-    import torch
+    torch = _torch()
     B, n_obs, Hq, d = q_obs.shape
     paged = page_table is not None
     _on_gpu(q_obs, k=k, prompt_lens=prompt_lens, page_table=page_table, votes=votes,
@@ -481,17 +503,19 @@ def md_snapkv_votes(q_obs, k, prompt_lens, *, max_prompt_len=None, page_table=No
                     sm_scale=0.0, votes=None, workspace=None, stream=None):
     """Raw SnapKV votes [B, Hkv, stride] fp32 of every prefix position
     (q_obs [B, n_obs, Hq, d]; k contiguous or paged; see include/magicdec.h)."""
-    import torch
+    torch = _torch()
     lib = load_library()
-    kw = dict(max_prompt_len=max_prompt_len, page_table=page_table, sm_scale=sm_scale)
+    a = make_snapkv_args(q_obs, k, prompt_lens, max_prompt_len=max_prompt_len,
+                         page_table=page_table, sm_scale=sm_scale, votes=votes,
+                         workspace=workspace)
     if votes is None:
-        stride = make_snapkv_args(q_obs, k, prompt_lens, **kw).votes_stride
-        votes = torch.zeros((q_obs.shape[0], k.shape[2], stride), dtype=torch.float32,
+        votes = torch.zeros((q_obs.shape[0], k.shape[2], a.votes_stride), dtype=torch.float32,
                             device=q_obs.device)
+        a.votes = votes.data_ptr()
     if workspace is None:
-        need = md_snapkv_workspace_bytes(q_obs, k, prompt_lens, **kw)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q_obs.device)
-    a = make_snapkv_args(q_obs, k, prompt_lens, votes=votes, workspace=workspace, **kw)
+        need = max(lib.md_snapkv_workspace_bytes(ctypes.byref(a)), 256)
+        workspace = q_obs.new_empty((need,), dtype=torch.uint8)
+        a.workspace, a.workspace_bytes = workspace.data_ptr(), need
     _check(lib.md_snapkv_votes(ctypes.byref(a), _stream_handle(q_obs, stream)))
     return votes
 
@@ -501,7 +525,7 @@ def md_snapkv_select(votes, prompt_lens, n_obs, budget, *, pool=5, idx=None, idx
                      stream=None):
     """Pool the votes [B, Hkv, stride] and keep budget positions per (sequence,
     kv head): returns (idx [B, Hkv, budget] int32 ascending, idx_len [B] int32)."""
-    import torch
+    torch = _torch()
     lib = load_library()
     B, Hkv, stride = votes.shape
     if votes.dtype != torch.float32 or not votes.is_contiguous():
@@ -553,7 +577,7 @@ def md_merge_lse(o_parts, lse_parts, *, out_dtype=None, out=None, lse=None, stre
 def make_kv_cache(k, v, *, num_seqs=None, page_table=None) -> MdKvCache:
     """Fill md_kv_cache from the cache tensors: contiguous [B, S_alloc, Hkv, d]
     or, with page_table [B, max_pages] int32, paged [P, page_size, Hkv, d]."""
-    import torch
+    torch = _torch()
     if k.dim() != 4 or k.shape != v.shape or k.stride() != v.stride() or k.stride(3) != 1:
         raise ValueError("k and v must be 4-D with equal shapes and strides, head_dim unit-stride")
     _on_gpu(k, v=v, page_table=page_table)
@@ -586,7 +610,7 @@ def make_kv_cache(k, v, *, num_seqs=None, page_table=None) -> MdKvCache:
 def md_kv_append(k, v, k_new, v_new, pos0, *, page_table=None, lens_out=None, stream=None):
     """Write k_new/v_new [B, n_new, Hkv, d] at positions pos0[b] + i of the cache
     (in place).  Returns lens_out [B] int32 = pos0 + n_new."""
-    import torch
+    torch = _torch()
     lib = load_library()
     B, n_new = k_new.shape[:2]
     if k_new.shape != v_new.shape or not k_new.is_contiguous() or not v_new.is_contiguous():
@@ -611,7 +635,7 @@ def md_greedy_accept(logits, draft, *, accepted=None, tokens=None, target=None,
                      want_target=True, workspace=None, stream=None):
     """logits [B, gamma + 1, vocab] float32/bfloat16, draft [B, gamma] int32 ->
     (accepted [B], tokens [B, gamma + 1], target [B, gamma + 1] or None), int32."""
-    import torch
+    torch = _torch()
     lib = load_library()
     B, L, vocab = logits.shape
     if not logits.is_contiguous():
@@ -666,7 +690,7 @@ def md_kv_commit(lens, accepted, q_len, *, idx=None, ring_start=0, ring_len=None
 def md_streaming_list(prompt_lens, num_kv_heads, n_sink, window, *, idx=None, idx_len=None,
                       stream=None):
     """Sink-plus-window draft lists [B, Hkv, n_sink + window] and idx_len [B]."""
-    import torch
+    torch = _torch()
     lib = load_library()
     B = prompt_lens.shape[0]
     dev = prompt_lens.device
@@ -689,7 +713,7 @@ def md_kv_gather(dst_k, dst_v, src_k, src_v, idx, idx_len, src_lens, *, dst_page
     """Gather each (sequence, kv head)'s listed rows idx [B, Hkv, stride] of the
     src cache into rows 0.. of the dst cache (in place), zeros for entries
     outside [0, src_lens[b]).  Returns dst_lens [B] int32 = min(idx_len, stride)."""
-    import torch
+    torch = _torch()
     lib = load_library()
     B, Hkv, stride = idx.shape
     if idx.dtype != torch.int32 or not idx.is_contiguous():

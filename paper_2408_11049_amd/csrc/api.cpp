@@ -153,7 +153,8 @@ int run_attention(const md_attn_args* a, int mode, int n_sink, int window, void*
     a = &local;
   }
   if (a) workspace = a->workspace;
-  int st = validate_attn(a, mode, n_sink, window);
+  Plan pl;
+  int st = validate_attn(a, mode, n_sink, window, &pl);
   if (st != MD_OK) return st;
   if (a->num_seqs == 0) return MD_OK;
   if (mode == MD_MODE_DRAFT_INDEXED) {
@@ -162,7 +163,6 @@ int run_attention(const md_attn_args* a, int mode, int n_sink, int window, void*
       return MD_ERR_INVALID_ARG;
   }
   const int num_cus = device_cu_count();
-  const Plan pl = plan_call(a, mode, n_sink, window, num_cus);
   const bool bf16 = a->dtype == MD_BF16;
   const bool paged = a->page_size != 0;
 

@@ -28,7 +28,7 @@ constexpr int kWaves = 4;
 constexpr int kWavesWide = 8;
 constexpr int kTile = 32;            // tokens per wave iteration
 constexpr int kMinChunkTokens = 128;  // shortest chunk of a split range: a tile per wave
-constexpr int64_t kWholeTokens = 256;  // ranges up to this are not split
+constexpr int64_t kWholeTokens = 512;  // ranges up to this are not split
 constexpr int64_t kWholeList = 1020;   // listed drafts: lists up to this are not split
 // Ranges up to this are split only for a caller that gives a workspace: they
 // fit one pass, so a call without one runs unsplit instead of being refused.
@@ -95,7 +95,9 @@ int check_attn_sizes(const md_attn_args* a);
 
 // Checks every argument the host can see.  Returns MD_OK or an md_status.
 // mode MD_MODE_DRAFT_INDEXED reads `window` as the list capacity idx_stride.
-int validate_attn(const md_attn_args* a, int mode, int n_sink, int window);
+// *plan (unless NULL) receives the call's plan when num_seqs > 0.
+int validate_attn(const md_attn_args* a, int mode, int n_sink, int window,
+                  Plan* plan = nullptr);
 
 // The decomposition for these sizes on a device with num_cus compute units.
 // Only sizes are read from `a`.  Call after validate_attn succeeded.

@@ -61,7 +61,7 @@ int check_attn_sizes(const md_attn_args* a) {
   return MD_OK;
 }
 
-int validate_attn(const md_attn_args* a, int mode, int n_sink, int window) {
+int validate_attn(const md_attn_args* a, int mode, int n_sink, int window, Plan* plan) {
   if (!a) return MD_ERR_INVALID_ARG;
   if (mode != MD_MODE_VERIFY && mode != MD_MODE_DRAFT && mode != MD_MODE_DRAFT_INDEXED)
     return MD_ERR_INVALID_ARG;
@@ -87,6 +87,7 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window) {
   if (a->num_seqs == 0) return MD_OK;  // nothing will be read or written
   const int num_cus = device_cu_count();
   const Plan p = plan_call(a, mode, n_sink, window, num_cus);
+  if (plan) *plan = p;
   if (p.n_chunks > kMaxChunks) return MD_ERR_UNSUPPORTED;  // unreachable below ~16k compute units
 
   if (!a->q || !a->k || !a->v || !a->o || !a->kv_lens) return MD_ERR_INVALID_ARG;
@@ -184,9 +185,12 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // MD_SLOTS_SCALE = 2..4 plans for that many workgroups per compute unit
   // (measurement only).
   const int64_t slots = (num_cus > 0 ? num_cus : 256) * std::max(1, env_knob("MD_SLOTS_SCALE", 2, 4));
-  // 256 tokens in one chunk take 8.9-10.2 us and in two 9.4-11.0 (the merge
-  // costs more than the second tile).  A listed draft keeps lists of up to
-  // kWholeList positions whole, so that they need no workspace.
+  // Up to kWholeTokens one pass does: 256 tokens in one chunk take 8.9-10.2 us
+  // and in two 9.4-11.0; at 430-512 the kernels gain 3 us of 13 but a caller
+  // issuing call after call loses 5 us of host time to the second launch (82
+  // units of 427 tokens through the binding: 17.4 us whole, 17.9 split).  A
+  // listed draft keeps lists of up to kWholeList positions whole, so that they
+  // need no workspace.
   whole = std::max(whole, mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
   p.hp = heads_per_workgroup(a, mode, U, slots, whole);
   p.n_groups = p.n_units / p.hp;

@@ -114,9 +114,9 @@ def test_fused_matches_separate_merge(monkeypatch):
     assert d <= TOL["bf16"] / 4
 
 
-# Ranges at the edges of the split (256 tokens stay whole; chunks of 128) and
+# Ranges at the edges of the split (512 tokens stay whole; chunks of 128) and
 # merges of 2 to 126 parts: Hkv, Hq, L, lens, d, dtype.
-EDGES = [(1, 4, 4, [255], 64, "f32"), (1, 4, 4, [256], 128, "bf16"), (1, 4, 4, [257], 128, "bf16"),
+EDGES = [(1, 4, 4, [511], 64, "f32"), (1, 4, 4, [512], 128, "bf16"), (1, 4, 4, [513], 128, "bf16"),
          (2, 8, 5, [1025, 300], 64, "bf16"), (1, 4, 1, [9 * 128], 128, "bf16"),
          (1, 8, 5, [32 * 128, 5], 128, "bf16"), (1, 4, 2, [33 * 128 - 1], 64, "f32"),
          (1, 2, 3, [16001], 128, "f32"), (1, 4, 1, [16100, 1, 700], 128, "bf16")]

@@ -16,8 +16,8 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libmagicdec.so")
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "plan.cpp", "costmodel.cpp", "attn.hip", "merge.hip", "snapkv.hip", "step.hip",
-           "bench.hip", "noalloc.hip"]
+SOURCES = ["api.cpp", "plan.cpp", "costmodel.cpp", "attn.hip", "attn_agpr.hip", "merge.hip",
+           "snapkv.hip", "step.hip", "bench.hip", "noalloc.hip"]
 
 
 def hipcc() -> str:
@@ -33,12 +33,11 @@ def _flags():
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-# Per-source flags.  snapkv.hip: MFMA results in VGPRs rather than AGPRs.
-# The SnapKV passes fit their register budgets either way, and the vector
-# work that reads each score then needs no copy out of an AGPR (32 per
-# 64-key tile and wave in the votes pass; measured 1.6% on the votes call,
-# votes identical).
-EXTRA_FLAGS = {"snapkv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# Per-source flags: MFMA results in VGPRs rather than AGPRs.  snapkv.hip: the
+# passes fit their register budgets either way, and the vector work that reads
+# each score then needs no copy out of an AGPR.  attn.hip: measured there.
+_MFMA_IN_VGPRS = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+EXTRA_FLAGS = {"snapkv.hip": _MFMA_IN_VGPRS, "attn.hip": _MFMA_IN_VGPRS}
 
 
 def _compile(src: str, verbose: bool) -> str:

@@ -40,6 +40,10 @@ constexpr int kMaxChunks = 65535;    // a split plan's arrival count fits 16 bit
 // the sequences by length, so it is kept to small batches of long caches.
 constexpr int kLptMaxSeqs = 256;
 constexpr int kLptMinLen = 4096;
+constexpr int kBalMinLen = 4608;  // the balanced verify of bf16 (fp32: kLptMinLen)
+constexpr double kMergeUs = 6.0;  // the merge launch of a split plan
+// Partial O and lse of a split that more than covers the compute units.
+constexpr int64_t kSplitMaxPartials = int64_t{24} << 20;
 // The balanced verify (same launches as longest-first) keeps its partial
 // results within this much workspace, else longest-first is used: enough
 // for one workgroup per compute unit on 256 of them at up to three row tiles
@@ -113,8 +117,7 @@ Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 // SnapKV selection: validation and the chunking of its two passes.
 constexpr int kSnapkvMaxRows = 256;  // G * n_obs
-constexpr int kSnapkvMinChunk = 128;    // keys: shortest chunk of a few units
-constexpr int kSnapkvLongChunk = 2048;  // keys: shortest chunk of many long units
+constexpr int kSnapkvMinChunk = 128;  // keys: shortest chunk
 struct SnapkvPlan {
   int32_t G = 0, R = 0, TW = 0;
   int32_t n_units = 0;

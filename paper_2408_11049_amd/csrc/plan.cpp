@@ -113,18 +113,61 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window, Plan*
   return MD_OK;
 }
 
-// The range split for n_groups workgroups' worth of units: one chunk each
-// when they alone cover every compute unit, else each range is cut just until
-// they do, never below kMinChunkTokens tokens per chunk (a tile for each wave:
-// on MI355X a 5-token verify of one 4001-token sequence takes 27.7 us in
-// 1024-token chunks, 16.2 in 256 and 15.0 in 128).  A range of at most `whole`
-// tokens is not cut.
+// What a launch of `wgs` workgroups of `bytes` K/V bytes each costs, in
+// microseconds, as measured on MI355X: `start` per round of resident
+// workgroups (first tile, epilogue), the stream at most at `wg_rate` bytes/us
+// per workgroup, kCuRate per compute unit and kChipRate altogether.
+// Workgroups past the resident ones wait for a whole round.
+struct StreamCost {
+  double start;      // us
+  double wg_rate;    // bytes/us of one workgroup
+  int resident;      // workgroups a compute unit holds
+};
+static double launch_us(const StreamCost& c, int64_t wgs, double bytes, int64_t cus) {
+  constexpr double kChipRate = 7.0e6, kCuRate = 34.0e3;
+  const int64_t round = cus * c.resident;
+  double us = 0.0;
+  for (int64_t left = wgs; left > 0; left -= round) {
+    const int64_t w = std::min(left, round);
+    const double per_cu = kCuRate / static_cast<double>(ceil_div(w, cus));
+    // Later rounds start as workgroups of the round before finish.
+    const double chip = kChipRate / static_cast<double>(w);
+    us += c.start + bytes / std::min(c.wg_rate, std::min(per_cu, chip));
+  }
+  return us;
+}
+
+// The range split for n_groups workgroups' worth of units of U tokens.  The
+// plain rule gives a group one chunk when the groups alone cover every compute
+// unit, else just as many as cover them, never below kMinChunkTokens tokens
+// per chunk (a tile for each wave: a 5-token verify of one 4001-token sequence
+// takes 27.7 us in 1024-token chunks, 16.2 in 256 and 15.0 in 128); a range of
+// at most `whole` tokens is not cut.  That leaves a second round of few
+// workgroups wherever the groups do not divide the compute units (40 sequences
+// of 8 heads and 3000 tokens: 64 of 320 workgroups run alone), so any other
+// count that the launch cost above puts at 5% less is taken instead.
 static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whole,
+                        const StreamCost* cost, int64_t group_rows, int64_t tok_bytes, int d,
                         int64_t* n_chunks_out, int64_t* chunk_len_out) {
   int64_t n_chunks = 1;
-  if (n_groups > 0 && n_groups < slots) {
-    const int64_t cap = U <= whole ? 1 : ceil_div(U, kMinChunkTokens);
-    n_chunks = std::min(ceil_div(slots, n_groups), cap);
+  const int64_t cap = U <= whole ? 1 : ceil_div(U, kMinChunkTokens);
+  if (n_groups > 0 && n_groups < slots) n_chunks = std::min(ceil_div(slots, n_groups), cap);
+  if (cost && n_groups > 0 && cap > 1 && n_groups < 2 * slots) {
+    auto us = [&](int64_t n) {
+      const double parts = n > 1 ? 2.0 * n * n_groups * group_rows * (d + 1) * 4 : 0.0;
+      const double chunk = static_cast<double>(ceil_div(ceil_div(U, n), kTile) * kTile);
+      return launch_us(*cost, n * n_groups, chunk * tok_bytes, slots) +
+             (n > 1 ? kMergeUs + parts / 6.0e6 : 0.0);
+    };
+    double best = us(n_chunks) * 0.95;
+    for (int64_t n = 1; n <= cap && n * n_groups <= 4 * slots; ++n) {
+      if (n * n_groups * group_rows * (d + 1) * 4 > kSplitMaxPartials) break;
+      const double t = us(n);
+      if (t < best) {
+        best = t;
+        n_chunks = n;
+      }
+    }
   }
   int64_t chunk_len = ceil_div(ceil_div(U, n_chunks), kTile) * kTile;
   if (chunk_len < kTile) chunk_len = kTile;
@@ -132,6 +175,24 @@ static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whol
   if (n_chunks < 1) n_chunks = 1;
   *n_chunks_out = n_chunks;
   *chunk_len_out = chunk_len;
+}
+
+// The launch cost of an attention instance.  Starts: 6.7 us measured with one
+// row tile, ~10 with two, 16 with four.  A workgroup streams 34 KB/us with up to
+// two row tiles (1.9 us per tile of its four waves), 24-28 with more; rows of
+// 64 channels halve the bytes of a tile, not its work.  Two workgroups fit a
+// compute unit's registers and LDS with up to two row tiles of bf16 or with 64
+// channels, else one.
+static StreamCost stream_cost(int NT, int d, bool bf16) {
+  StreamCost c;
+  c.start = 4.0 + 3.0 * NT;
+  if (bf16)
+    c.wg_rate = d == 128 ? (NT <= 2 ? 34.0e3 : (NT == 3 ? 28.0e3 : 24.0e3))
+                         : (NT <= 2 ? 27.0e3 : 22.0e3);
+  else
+    c.wg_rate = NT == 1 ? 27.0e3 : 27.0e3 / NT;
+  c.resident = (bf16 && NT <= 2) || (d == 64 && (bf16 || NT <= 2)) ? 2 : 1;
+  return c;
 }
 
 // Kv heads per workgroup.  In the token-major cache the kv heads of a token
@@ -150,7 +211,8 @@ static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whol
 // per head -- no adjacent rows -- and keeps one head per workgroup.
 // MD_HEADS_PER_WG (1 or 2) overrides, for measurement.
 static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64_t slots,
-                               int64_t whole) {
+                               int64_t whole, const StreamCost* cost, int64_t rows,
+                               int64_t tok_bytes) {
   const int forced = env_knob("MD_HEADS_PER_WG", 1, 2);
   if (a->num_kv_heads % 2) return 1;
   if (forced) return forced;
@@ -158,7 +220,8 @@ static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64
   const int64_t pairs = static_cast<int64_t>(a->num_seqs) * a->num_kv_heads / 2;
   if (pairs >= slots) return 2;
   int64_t n_chunks, chunk_len;
-  split_units(U, pairs, slots, whole, &n_chunks, &chunk_len);
+  split_units(U, pairs, slots, whole, cost, 2 * rows, 2 * tok_bytes, a->head_dim, &n_chunks,
+              &chunk_len);
   return chunk_len >= kPairMinChunkTokens ? 2 : 1;
 }
 
@@ -192,10 +255,19 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // listed draft keeps lists of up to kWholeList positions whole, so that they
   // need no workspace.
   whole = std::max(whole, mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
-  p.hp = heads_per_workgroup(a, mode, U, slots, whole);
+  const bool bf16 = a->dtype == MD_BF16;
+  const StreamCost sc = stream_cost(p.NT, a->head_dim, bf16);
+  const StreamCost* cost = env_knob("MD_SLOTS_SCALE", 2, 4) ? nullptr : &sc;
+  const int64_t tok_bytes = int64_t{2} * a->head_dim * (bf16 ? 2 : 4);
+  p.hp = heads_per_workgroup(a, mode, U, slots, whole, cost, p.R, tok_bytes);
   p.n_groups = p.n_units / p.hp;
   int64_t n_chunks, chunk_len;
-  split_units(U, p.n_groups, slots, whole, &n_chunks, &chunk_len);
+  // Long ranges of groups that cover the device are the balanced verify's (or
+  // longest-first's): one chunk.
+  const int bal_min = bf16 ? kBalMinLen : kLptMinLen;
+  if (p.n_groups >= slots && U >= bal_min) cost = nullptr;
+  split_units(U, p.n_groups, slots, whole, cost, p.hp * p.R, p.hp * tok_bytes, a->head_dim,
+              &n_chunks, &chunk_len);
   p.n_chunks = static_cast<int32_t>(n_chunks);
   p.chunk_len = static_cast<int32_t>(chunk_len);
   // Balanced verify: where the units alone fill the device and lengths may
@@ -213,7 +285,7 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   if (mode == MD_MODE_VERIFY && p.n_chunks == 1 && a->num_seqs >= 2 &&
       a->num_seqs <= kLptMaxSeqs && bal_knob != 1 && p.NT <= kBalMaxNT(a->dtype == MD_BF16) &&
       (bal_knob == 2 ||
-       (a->max_kv_len >= kLptMinLen && p.n_units / bal_hp <= 2 * cus))) {
+       (a->max_kv_len >= bal_min && p.n_units / bal_hp <= 2 * cus))) {
     const int hp = bal_hp;
     const int64_t groups = p.n_units / hp;
     // One workgroup per compute unit: every range then streams at once.
@@ -259,30 +331,72 @@ Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 namespace {
 
-// Chunks of a range of U keys over n_units units.  A few units are cut into
-// at most `fill` workgroups (what the device holds at once; one more than fits
-// starts a second round: 50 fp32 units of 256 rows, 258 us in 250 workgroups and
-// 416 in 300), down to kSnapkvMinChunk keys: below that the prologue of a
-// chunk costs more than its keys (one prompt of 4000 tokens, 8 heads of 128
-// rows: 49 us at 1024 keys a chunk, 19.4 at 256, 15.2 at 128, 16.2 at 64).
-// Long units are cut further, into whole rounds of `fill` up to sixteen
-// workgroups per compute unit, so that ragged lengths even out, while a chunk
-// keeps about kSnapkvLongChunk keys (64 prompts of 32768: 1700 us against 1764 with
-// two chunks a unit; 16 prompts of 16384, 64 rows: 185 us at 2048 keys a chunk
-// and 197 at 1024).
-void split_range(int64_t U, int64_t n_units, int64_t fill, int num_cus, int32_t* n_chunks_out,
-                 int32_t* chunk_len_out) {
-  int64_t n_chunks = 1;
+// What one SnapKV pass over chunks of `keys` keys costs in `wgs` workgroups, in
+// microseconds, as measured on MI355X: a compute unit takes key_us per key when
+// at least `busy` workgroups share it (its workgroups then take turns: the most
+// loaded unit sets the time), every round of `resident` ones start_us, and
+// unequal speeds waste some of the last workgroup of each unit.
+struct PassCost {
+  double key_us, start_us;
+  int busy, resident;
+};
+double pass_us(const PassCost& c, int64_t wgs, int64_t keys, int64_t cus) {
+  constexpr double uneven = 0.15;
+  const int64_t per_cu = std::max<int64_t>(ceil_div(wgs, cus), c.busy);
+  const double stream = static_cast<double>(keys) * c.key_us * static_cast<double>(per_cu);
+  return stream * (1.0 + uneven * static_cast<double>(cus) / static_cast<double>(wgs)) +
+         c.start_us * static_cast<double>(ceil_div(wgs, cus * c.resident));
+}
+
+// Chunks of a range of U keys over n_units units: the fewest within 1% of the
+// least pass_us, down to kSnapkvMinChunk keys a chunk (one prompt of 4000
+// tokens, 8 heads of 128 rows: 49 us at 1024 keys a chunk, 19.4 at 256, 15.2 at
+// 128, 16.2 at 64) and up to sixteen workgroups per compute unit (64 prompts of
+// 32768: 1700 us with eight chunks a unit, 1764 with two).
+void split_range(int64_t U, int64_t n_units, const PassCost& cost, int64_t cus,
+                 int32_t* n_chunks_out, int32_t* chunk_len_out) {
+  const int64_t whole = ceil_div(U > 0 ? U : 1, kTile) * kTile;
+  int64_t chunk_len = whole;
   if (n_units > 0) {
-    n_chunks = std::max<int64_t>(1, std::min(fill / n_units, ceil_div(U, kSnapkvMinChunk)));
-    const int64_t longest = ceil_div(U, kSnapkvLongChunk);
-    for (int64_t total = fill; total <= 16 * int64_t{num_cus}; total += fill)
-      if (total / n_units <= longest) n_chunks = std::max(n_chunks, total / n_units);
+    double best = pass_us(cost, n_units, whole, cus);
+    for (int64_t n = 2; n * n_units <= 16 * cus;) {
+      const int64_t len = ceil_div(ceil_div(U, n), kTile) * kTile;
+      if (len < kSnapkvMinChunk) break;
+      const int64_t n_len = ceil_div(U, len);
+      const double t = pass_us(cost, n_len * n_units, len, cus);
+      if (t < 0.99 * best) {
+        best = t;
+        chunk_len = len;
+      }
+      // The next shorter length, in steps of a sixteenth.
+      n = std::max(n_len + 1, ceil_div(U, std::max<int64_t>(kTile, len - std::max<int64_t>(
+                                                 kTile, len / 16 / kTile * kTile))));
+    }
   }
-  int64_t chunk_len = ceil_div(ceil_div(U > 0 ? U : 1, n_chunks), kTile) * kTile;
-  n_chunks = ceil_div(U > 0 ? U : 1, chunk_len);
-  *n_chunks_out = static_cast<int32_t>(n_chunks);
+  *n_chunks_out = static_cast<int32_t>(ceil_div(U > 0 ? U : 1, chunk_len));
   *chunk_len_out = static_cast<int32_t>(chunk_len);
+}
+
+// key_us: the scores of a key (0.013 us at 128 rows in bf16, 0.107 in fp32,
+// d = 128) or its bytes, whichever takes longer.  start_us grows with the rows
+// of Q a workgroup loads: 50 fp32 units of 256 rows take 258 us in 250
+// workgroups, one round, and 322 in 1000.  Residency as the registers and LDS of
+// the pass instances allow.
+PassCost pass_cost(int R, int d, bool f32) {
+  const double rows = R / 128.0, wide = d / 128.0;
+  PassCost c;
+  if (f32) {
+    c.key_us = 0.107 * std::max(rows, 0.125) * wide;
+    c.start_us = 4.0 + 15.0 * rows * wide;
+    c.resident = R <= 128 ? (d == 64 ? 4 : 2) : (d == 64 ? 2 : 1);
+    c.busy = R <= 64 && d == 64 ? 2 : 1;
+  } else {
+    c.key_us = std::max(0.0094 * wide, 0.013 * rows);
+    c.start_us = 3.0 + 4.0 * rows;
+    c.resident = R <= 32 ? 4 : (R <= 64 ? 6 : (R <= 128 ? 4 : 2));
+    c.busy = R <= 64 ? 4 : (R <= 128 ? 3 : 2);
+  }
+  return c;
 }
 
 }  // namespace
@@ -333,18 +447,11 @@ SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus) {
   p.R = p.G * a->n_obs;
   p.TW = p.R <= 64 ? 1 : (p.R <= 128 ? 2 : 4);
   p.n_units = a->num_seqs * a->num_kv_heads;
-  // Workgroups that fill the device: four per compute unit, fewer where a
-  // workgroup holds more of it -- the 129-256-row instances (eight waves in
-  // bf16: 63 us against 70 with four per compute unit on four 70B-shaped
-  // prompts of 5000-12000 tokens) and the fp32 ones, whose tiles take twice
-  // the LDS and registers (256 rows: one resident workgroup).
   const int64_t cus = num_cus > 0 ? num_cus : 256;
-  const bool f32 = a->dtype == MD_F32;
-  const int64_t fill = cus * (p.R <= 64 ? 4 : (p.R <= 128 ? (f32 ? 2 : 4) : (f32 ? 1 : 2)));
-  split_range(a->max_prompt_len, p.n_units, fill, static_cast<int>(cus), &p.n_chunks_stats,
-              &p.chunk_len_stats);
-  split_range(a->max_prompt_len - a->n_obs, p.n_units, fill, static_cast<int>(cus),
-              &p.n_chunks_votes, &p.chunk_len_votes);
+  const PassCost cost = pass_cost(p.R, a->head_dim, a->dtype == MD_F32);
+  split_range(a->max_prompt_len, p.n_units, cost, cus, &p.n_chunks_stats, &p.chunk_len_stats);
+  split_range(a->max_prompt_len - a->n_obs, p.n_units, cost, cus, &p.n_chunks_votes,
+              &p.chunk_len_votes);
   p.part_bytes = align_up(static_cast<size_t>(p.n_units) * p.n_chunks_stats * p.R * 4, 256);
   p.lse_bytes = align_up(static_cast<size_t>(p.n_units) * p.R * 4, 256);
   p.workspace_bytes = 2 * p.part_bytes + p.lse_bytes;

@@ -157,3 +157,22 @@ def test_short_ranges_without_a_workspace():
         torch.cuda.synchronize()
         compare(out.float().cpu().numpy().astype(np.float64),
                 lse.cpu().numpy().astype(np.float64), *ref, "bf16", f"workspace {nbytes}")
+
+
+# Splits that more than cover the compute units: units that leave a second round
+# nearly empty (B * Hkv = 320 of 256), and 64-channel rows of three and four row
+# tiles, two workgroups per compute unit.  B, Hkv, Hq, L, lens, d, page.
+PAST_SLOTS = [(40, 8, 8, 1, [3000 - 25 * i for i in range(40)], 128, 16),
+              (4, 8, 64, 8, [8000, 5001, 100, 7999], 64, 16),
+              (4, 8, 64, 5, [16000, 9000, 15999, 40], 64, 0)]
+
+
+@pytest.mark.parametrize("case", PAST_SLOTS, ids=[f"past{i}" for i in range(len(PAST_SLOTS))])
+def test_splits_past_the_compute_units(case):
+    B, Hkv, Hq, L, lens, d, page = case
+    c = wl.make_case(B=B, q_len=L, Hq=Hq, Hkv=Hkv, d=d, kv_lens=lens, dtype="bf16", page_size=page,
+                     seed=740 + B, device=DEV, S_alloc=None if page else max(lens) + 5)
+    need = _need(oracle.VERIFY, c)
+    say(f"[past-slots] {case[:4]} d={d} workspace {need} B")
+    assert need > B * L * Hq * (d + 1) * 4, "the case must split its range"
+    compare(*_call(oracle.VERIFY, c, None), *run_oracle(oracle.VERIFY, c), "bf16", str(case[:4]))

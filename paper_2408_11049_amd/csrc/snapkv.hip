@@ -692,19 +692,20 @@ constexpr int kSelPer = 4;             // global instance: consecutive positions
 constexpr int kSelStep = kSelThreads * kSelPer;
 constexpr int kSelRegThreads = 1024;   // register instance: threads per workgroup
 constexpr int kSelRegWaves = kSelRegThreads / 64;
-constexpr int kSelKpt = 33;            // and pooled keys per thread
-constexpr int kSelPadW = 2;            // LDS pad words per segment: odd stride 35
-constexpr int kSelRegKeys = kSelRegThreads * kSelKpt;  // its longest row: 33792 prefix positions
+constexpr int kSelPadW = 2;            // LDS pad words per segment (odd strides 11, 19, 35)
+constexpr int kSelRegKeys = kSelRegThreads * 33;  // its longest row: 33792 prefix positions
+constexpr int kSelHists = 2;           // radix histograms, shared by the waves w % kSelHists
 constexpr int kSelRegHalo = 3;         // and its widest pooling: pool <= 7
 
-// Count every active lane's bin in the wave's histogram h.  Pooled votes of
-// similar size share their top key bits, so the early radix passes pile
-// onto a few bins: the bin of the lowest uncounted lane goes in with one
-// atomic for all lanes that share it, twice (with skewed keys, most likely
-// the wave's most common bins), and the remaining lanes add directly.
+// Count every active lane's bin in the histogram h.  Pooled votes of similar
+// size share their top key bits, so the early radix passes pile onto a few
+// bins: the bin of the lowest active lane goes in with one atomic for all lanes
+// that share it, ROUNDS times, and the remaining lanes add directly.
+template <int ROUNDS>
 __device__ __forceinline__ void sk_hist_add(uint32_t* h, bool active, uint32_t bin, int lane) {
   bool mine = active;  // this lane's key is not counted yet
-  for (int round = 0; round < 2; ++round) {
+#pragma unroll
+  for (int round = 0; round < ROUNDS; ++round) {
     const uint64_t pending = __ballot(mine);
     if (pending == 0) return;  // wave-uniform
     const int leader = __ffsll(static_cast<long long>(pending)) - 1;
@@ -742,9 +743,11 @@ __device__ __forceinline__ uint32_t sk_block_scan(uint32_t x, uint32_t* wsum, ui
 // The keep-th largest key of a row and how many keys exceed it, by radix
 // select over 11-, 11- and 10-bit digits, most significant first:
 // `key_at(e)` is this thread's e-th key (0 <= e < PER), valid(e) whether it
-// is a position of the row; THREADS threads per workgroup.  hist is one
-// histogram of kSelBins counters per wave (LDS).  Every thread returns the
-// same (tau, above).
+// is a position of the row; THREADS threads per workgroup.  hist is kSelHists
+// histograms of kSelBins counters (LDS, 16-byte aligned); fewer of them than
+// waves, since clearing and adding up one per wave cost as much as the counting
+// (512 rows of 32736 votes: 76 us with 16, 62 with 4, 57 with 2).
+// Every thread returns the same (tau, above).
 constexpr int kSelBins = 2048;
 template <int PER, int THREADS, typename KeyAt, typename Valid>
 __device__ __forceinline__ void sk_radix_select(KeyAt key_at, Valid valid, int keep,
@@ -759,13 +762,14 @@ __device__ __forceinline__ void sk_radix_select(KeyAt key_at, Valid valid, int k
     const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
     const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
     const uint32_t hi_mask = pass == 0 ? 0u : (pass == 1 ? 0xffe00000u : 0xfffffc00u);
-    for (int i = tid; i < WAVES * kSelBins; i += THREADS) hist[i] = 0;
+    for (int i = tid; i < kSelHists * kSelBins / 4; i += THREADS)
+      reinterpret_cast<sk_u32x4*>(hist)[i] = sk_u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       const uint32_t k = key_at(e);
       const bool act = valid(e) && (k & hi_mask) == (prefix & hi_mask);
-      sk_hist_add(hist + w * kSelBins, act, (k >> shift) & dmask, lane);
+      sk_hist_add<1>(hist + (w % kSelHists) * kSelBins, act, (k >> shift) & dmask, lane);
     }
     __syncthreads();
     // Thread t owns digits kSelBins-1-4t .. kSelBins-4-4t (descending); a scan
@@ -776,7 +780,7 @@ __device__ __forceinline__ void sk_radix_select(KeyAt key_at, Valid valid, int k
     for (int i = 0; i < kDigitsPerThread; ++i) {
       const int d = kSelBins - 1 - (kDigitsPerThread * tid + i);
       c[i] = 0;
-      for (int x = 0; x < WAVES; ++x) c[i] += hist[x * kSelBins + d];
+      for (int x = 0; x < kSelHists; ++x) c[i] += hist[x * kSelBins + d];
       cnt += c[i];
     }
     uint32_t total;
@@ -801,59 +805,62 @@ __device__ __forceinline__ void sk_radix_select(KeyAt key_at, Valid valid, int k
 
 // Register instance, rows of at most kSelRegKeys prefix positions: 1024
 // threads, four waves per SIMD (measured 22% faster than 512 threads with
-// twice the keys each).  Thread t owns the contiguous segment [33t, 33t + 33)
-// of the row.  The raw votes are copied into LDS with 16-byte global loads,
-// position j at word j + 2 (j / 33) (two pad words per segment: an odd stride
-// of 35, so the 64 lanes reading the same offset of their segments hit
+// twice the keys each).  Thread t owns the contiguous segment
+// [KPT t, KPT t + KPT) of the row, KPT = 9, 17 or 33 by the row's capacity (a
+// thread works through all KPT keys whatever the row holds: 1024 rows of 4064
+// votes take 41 us with 9 keys a thread, 107 with 33).  The raw votes are copied into LDS with 16-byte global loads,
+// position j at word j + 2 (j / KPT) (two pad words per segment: an odd
+// stride, so the 64 lanes reading the same offset of their segments hit
 // distinct banks); each thread pools its segment from its own window of LDS
-// in sk_pooled's order and keeps the 33 keys in registers for the radix
+// in sk_pooled's order and keeps its keys in registers for the radix
 // passes and the compaction.  The positions a thread keeps are contiguous in
 // its segment, so two block scans give every thread its output offset and
 // the row comes out ascending.
-__device__ __forceinline__ int sk_pad(int j) { return j + kSelPadW * (j / kSelKpt); }
+template <int KPT>
+__device__ __forceinline__ int sk_pad(int j) { return j + kSelPadW * (j / KPT); }
 
-template <int POOL>
+template <int POOL, int KPT>
 __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const SnapkvSelectParams p) {
   // The raw votes, then (the keys in registers) the radix histograms.
-  constexpr int kBuf = kSelRegKeys + kSelPadW * kSelRegThreads;
-  __shared__ float buf[kBuf];
-  static_assert(kSelRegWaves * kSelBins <= kBuf, "histograms fit the buffer");
+  constexpr int kBuf = (KPT + kSelPadW) * kSelRegThreads;
+  __shared__ __attribute__((aligned(16))) float buf[kBuf];
+  static_assert(kSelHists * kSelBins <= kBuf, "histograms fit the buffer");
   __shared__ uint32_t wsum[kSelRegWaves];
   __shared__ uint32_t s_prefix, s_above;
 
   const int row = blockIdx.x;
   const int b = row / p.rows_per_seq;
   const int S = min(max(p.lens[b], 0), p.stride + p.n_obs);
-  const int n = max(S - p.n_obs, 0);  // <= stride <= kSelRegKeys
+  const int n = max(S - p.n_obs, 0);  // <= stride <= KPT * kSelRegThreads
   const int keep = min(p.budget - p.n_obs, n);
   const float* v = p.votes + static_cast<int64_t>(row) * p.stride;
   int32_t* out = p.idx + static_cast<int64_t>(row) * p.budget;
   const int tid = threadIdx.x;
   const int w = tid >> 6;
   const int lane = tid & 63;
-  const int j0 = tid * kSelKpt;  // this thread's segment
+  const int j0 = tid * KPT;  // this thread's segment
 
-  uint32_t key[kSelKpt];
+  uint32_t key[KPT];
   if (keep > 0) {
     const bool vec = (reinterpret_cast<uintptr_t>(v) & 15u) == 0;
     const int n4 = vec ? n / 4 : 0;
 #pragma unroll 4
     for (int i = tid; i < n4; i += kSelRegThreads) {
       const float4 x = reinterpret_cast<const float4*>(v)[i];
-      buf[sk_pad(4 * i)] = x.x;
-      buf[sk_pad(4 * i + 1)] = x.y;
-      buf[sk_pad(4 * i + 2)] = x.z;
-      buf[sk_pad(4 * i + 3)] = x.w;
+      buf[sk_pad<KPT>(4 * i)] = x.x;
+      buf[sk_pad<KPT>(4 * i + 1)] = x.y;
+      buf[sk_pad<KPT>(4 * i + 2)] = x.z;
+      buf[sk_pad<KPT>(4 * i + 3)] = x.w;
     }
-    for (int j = 4 * n4 + tid; j < n; j += kSelRegThreads) buf[sk_pad(j)] = v[j];
+    for (int j = 4 * n4 + tid; j < n; j += kSelRegThreads) buf[sk_pad<KPT>(j)] = v[j];
     __syncthreads();
-    // Raw vote at segment offset o (-POOL/2 <= o < 33 + POOL/2) of this
+    // Raw vote at segment offset o (-POOL/2 <= o < KPT + POOL/2) of this
     // thread's window, +0 outside the prefix; the word index stays inside the
     // buffer.
-    const int base = j0 + kSelPadW * tid;  // sk_pad(j0)
+    const int base = j0 + kSelPadW * tid;  // sk_pad<KPT>(j0)
     auto raw = [&](int o) -> float {
       const int jj = j0 + o;
-      const int seg = o < 0 ? -kSelPadW : (o >= kSelKpt ? kSelPadW : 0);
+      const int seg = o < 0 ? -kSelPadW : (o >= KPT ? kSelPadW : 0);
       const float x = buf[min(max(base + o + seg, 0), kBuf - 1)];  // always inside the buffer
       return (jj >= 0 && jj < n) ? x : 0.f;
     };
@@ -862,7 +869,7 @@ __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const
     // sum as sk_pooled forms it.
     constexpr int h = POOL / 2;
 #pragma unroll
-    for (int e = 0; e < kSelKpt; ++e) {
+    for (int e = 0; e < KPT; ++e) {
       float acc = 0.f;
 #pragma unroll
       for (int t = -h; t <= h; ++t) acc += raw(e + t);
@@ -870,7 +877,7 @@ __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < kSelKpt; ++e) key[e] = 0u;
+    for (int e = 0; e < KPT; ++e) key[e] = 0u;
   }
   __syncthreads();  // every raw read is done: the buffer holds the histograms now
 
@@ -880,7 +887,7 @@ __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const
   // compaction below look at the position).
   uint32_t tau = 0, above = 0;
   if (keep > 0)
-    sk_radix_select<kSelKpt, kSelRegThreads>(
+    sk_radix_select<KPT, kSelRegThreads>(
         [&](int e) { return key[e]; }, [](int) { return true; }, keep,
         reinterpret_cast<uint32_t*>(buf), wsum, &s_prefix, &s_above, tau, above);
   const uint32_t need_eq = keep > 0 ? static_cast<uint32_t>(keep) - above : 0;
@@ -890,7 +897,7 @@ __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const
     // before it; ties go to the smaller position.
     uint32_t n_gt = 0, n_eq = 0;
 #pragma unroll
-    for (int e = 0; e < kSelKpt; ++e) {
+    for (int e = 0; e < KPT; ++e) {
       n_gt += key[e] > tau;  // never a position past the row (key 0)
       n_eq += j0 + e < n && key[e] == tau;
     }
@@ -902,7 +909,7 @@ __global__ void __launch_bounds__(kSelRegThreads) snapkv_select_reg_kernel(const
     uint32_t pos = sk_block_scan<kSelRegWaves>(n_gt + eq_take, wsum, take_total, lane, w);
     uint32_t eq_left = eq_take;
 #pragma unroll
-    for (int e = 0; e < kSelKpt; ++e) {
+    for (int e = 0; e < KPT; ++e) {
       const bool eq = j0 + e < n && key[e] == tau;
       const bool take = key[e] > tau || (eq && eq_left > 0);
       eq_left -= (eq && eq_left > 0) ? 1u : 0u;
@@ -955,7 +962,7 @@ __global__ void __launch_bounds__(kSelThreads) snapkv_select_kernel(const Snapkv
 #pragma unroll
         for (int e = 0; e < kSelPer; ++e) {
           const bool act = base + e * kSelThreads + tid < n && (k[e] & hi_mask) == (prefix & hi_mask);
-          sk_hist_add(hist[w], act, (k[e] >> shift) & 255u, lane);
+          sk_hist_add<2>(hist[w], act, (k[e] >> shift) & 255u, lane);
         }
       }
       __syncthreads();
@@ -1130,12 +1137,22 @@ hipError_t launch_snapkv_select(const SnapkvSelectParams& p, hipStream_t s) {
   if (p.rows <= 0) return hipSuccess;
   const dim3 grid(p.rows), block(kSelThreads), rblock(kSelRegThreads);
   if (p.stride <= kSelRegKeys && p.pool / 2 <= kSelRegHalo) {
+#define MD_SELECT(POOL)                                                                         \
+  do {                                                                                          \
+    if (p.stride <= 9 * kSelRegThreads)                                                         \
+      hipLaunchKernelGGL((snapkv_select_reg_kernel<POOL, 9>), grid, rblock, 0, s, p);           \
+    else if (p.stride <= 17 * kSelRegThreads)                                                   \
+      hipLaunchKernelGGL((snapkv_select_reg_kernel<POOL, 17>), grid, rblock, 0, s, p);          \
+    else                                                                                        \
+      hipLaunchKernelGGL((snapkv_select_reg_kernel<POOL, 33>), grid, rblock, 0, s, p);          \
+  } while (0)
     switch (p.pool) {  // odd, checked by the caller
-      case 1: hipLaunchKernelGGL(snapkv_select_reg_kernel<1>, grid, rblock, 0, s, p); break;
-      case 3: hipLaunchKernelGGL(snapkv_select_reg_kernel<3>, grid, rblock, 0, s, p); break;
-      case 5: hipLaunchKernelGGL(snapkv_select_reg_kernel<5>, grid, rblock, 0, s, p); break;
-      default: hipLaunchKernelGGL(snapkv_select_reg_kernel<7>, grid, rblock, 0, s, p); break;
+      case 1: MD_SELECT(1); break;
+      case 3: MD_SELECT(3); break;
+      case 5: MD_SELECT(5); break;
+      default: MD_SELECT(7); break;
     }
+#undef MD_SELECT
   } else {
     hipLaunchKernelGGL(snapkv_select_kernel, grid, block, 0, s, p);
   }

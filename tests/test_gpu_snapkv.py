@@ -150,6 +150,17 @@ def test_select_exact(case):
         assert np.array_equal(idx.reshape(B * Hkv, budget)[r, : cnt[b]], ridx[r, : rcnt[r]]), r
 
 
+# Rows at the edges of the register instances (9, 17 and 33 keys per thread).
+SELECT_EDGES = [(1, 9216, 32, 700, 5, [9248], 2), (1, 9217, 32, 700, 5, [9249], 2),
+                (2, 17408, 16, 2049, 7, [17424, 9300], 1), (2, 17409, 16, 2049, 3, [17425, 40], 1),
+                (1, 33792, 32, 2049, 5, [33824], 2, 3), (1, 9217, 8, 9000, 1, [9225], 2, 1)]
+
+
+@pytest.mark.parametrize("case", SELECT_EDGES, ids=[f"edge{i}" for i in range(len(SELECT_EDGES))])
+def test_select_instance_edges(case):
+    test_select_exact(case)
+
+
 # (sequence, kv head) units sampled from the 64 x 8 of the full prompt shape.
 FULL_UNITS = [(0, 0), (5, 3), (13, 7), (22, 1), (37, 5), (44, 2), (51, 6), (63, 4)]
 

@@ -145,7 +145,8 @@ typedef struct {
  * these arguments and the workspace is missing, smaller or not 256-byte
  * aligned (which calls need one -- split ranges, the balanced verify --
  * depends on the sizes and the device, so size it for every new shape; ranges
- * of at most 1024 tokens run unsplit, more slowly, without one);
+ * of at most 1024 tokens, and outside the balanced verify units that cover the
+ * compute units by themselves, run unsplit, more slowly, without one);
  * MD_ERR_HIP.
  */
 int md_verify_attn(const md_attn_args* a, void* stream);
@@ -238,8 +239,10 @@ size_t md_workspace_bytes_indexed(const md_attn_args* a, int32_t idx_stride);
  *     buffer address once (hipGetSymbolAddress).
  *   - All calls on one GPU share its buffer, which keeps the last call's
  *     contents; nothing in it needs clearing (the counters carry a per-call
- *     tag).  Ranges of at most 1024 tokens run unsplit and leave it alone.  Calls that can overlap in time on one GPU (other streams, other
- *     threads) race on it and give wrong results: serialise them.
+ *     tag).  Calls that md_verify_attn or md_draft_attn would run without a
+ *     workspace run unsplit and leave it alone.  Others that can overlap in
+ *     time on one GPU (other streams, other threads) race on it and give
+ *     wrong results: serialise them.
  *   - `stream` (NULL: the null stream) must belong to the current device.
  * Errors: as md_verify_attn / md_draft_attn; MD_ERR_INVALID_ARG for another
  * mode or a stream of another device; MD_ERR_WORKSPACE for a plan larger than

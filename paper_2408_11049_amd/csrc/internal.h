@@ -28,11 +28,9 @@ constexpr int kWaves = 4;
 constexpr int kWavesWide = 8;
 constexpr int kTile = 32;            // tokens per wave iteration
 constexpr int kMinChunkTokens = 128;  // shortest chunk of a split range: a tile per wave
+constexpr int kPlainChunkTokens = 1024;  // the same of a plain plan (make_plan)
 constexpr int64_t kWholeTokens = 512;  // ranges up to this are not split
 constexpr int64_t kWholeList = 1020;   // listed drafts: lists up to this are not split
-// Ranges up to this are split only for a caller that gives a workspace: they
-// fit one pass, so a call without one runs unsplit instead of being refused.
-constexpr int64_t kSplitNeedsWorkspace = 1024;
 constexpr int kMaxRows = 64;         // G*L bound: at most four 16-row tiles
 constexpr int kPairMinChunkTokens = 4096;  // head pairs on split ranges: chunks at least this long
 constexpr int kMaxChunks = 65535;    // a split plan's arrival count fits 16 bits
@@ -106,13 +104,14 @@ int validate_attn(const md_attn_args* a, int mode, int n_sink, int window,
 // The decomposition for these sizes on a device with num_cus compute units.
 // Only sizes are read from `a`.  Call after validate_attn succeeded.
 // mode MD_MODE_DRAFT_INDEXED reads `window` as the list capacity idx_stride.
-// Ranges of at most `whole` tokens are not split.
+// A plain plan splits a range only where the units alone leave compute units
+// idle, into chunks of at least kPlainChunkTokens: the form that asks for the
+// least workspace.
 Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus,
-               int64_t whole = 0);
+               bool plain = false);
 
-// The decomposition a call runs: make_plan, or its unsplit form when the range
-// fits one pass (kSplitNeedsWorkspace) and the caller's workspace does not
-// serve the split.
+// The decomposition a call runs: make_plan, or the plain plan when the caller's
+// workspace does not serve the split and that needs none.
 Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus);
 
 // SnapKV selection: validation and the chunking of its two passes.

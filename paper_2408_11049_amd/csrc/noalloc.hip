@@ -73,8 +73,8 @@ extern "C" int md_attn_noalloc(const md_attn_args* a, int32_t mode, int32_t n_si
   }
   void* ws = md::scratch_address(dev, &e);
   if (!ws) return md::hip_fail(e);
-  // A range that fits one pass is not split here: such calls leave the shared
-  // scratch alone, so they may overlap.
+  // A call that can run without a workspace does so here: it leaves the shared
+  // scratch alone, so such calls may overlap.
   md_attn_args local = *a;
   local.workspace = nullptr;
   local.workspace_bytes = 0;

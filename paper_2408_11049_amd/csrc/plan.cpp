@@ -139,18 +139,18 @@ static double launch_us(const StreamCost& c, int64_t wgs, double bytes, int64_t 
 
 // The range split for n_groups workgroups' worth of units of U tokens.  The
 // plain rule gives a group one chunk when the groups alone cover every compute
-// unit, else just as many as cover them, never below kMinChunkTokens tokens
-// per chunk (a tile for each wave: a 5-token verify of one 4001-token sequence
+// unit, else just as many as cover them, never below `min_chunk` tokens
+// per chunk (kMinChunkTokens, a tile for each wave: a 5-token verify of one 4001-token sequence
 // takes 27.7 us in 1024-token chunks, 16.2 in 256 and 15.0 in 128); a range of
 // at most `whole` tokens is not cut.  That leaves a second round of few
 // workgroups wherever the groups do not divide the compute units (40 sequences
 // of 8 heads and 3000 tokens: 64 of 320 workgroups run alone), so any other
 // count that the launch cost above puts at 5% less is taken instead.
 static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whole,
-                        const StreamCost* cost, int64_t group_rows, int64_t tok_bytes, int d,
+                        int64_t min_chunk, const StreamCost* cost, int64_t group_rows, int64_t tok_bytes, int d,
                         int64_t* n_chunks_out, int64_t* chunk_len_out) {
   int64_t n_chunks = 1;
-  const int64_t cap = U <= whole ? 1 : ceil_div(U, kMinChunkTokens);
+  const int64_t cap = U <= whole ? 1 : ceil_div(U, min_chunk);
   if (n_groups > 0 && n_groups < slots) n_chunks = std::min(ceil_div(slots, n_groups), cap);
   if (cost && n_groups > 0 && cap > 1 && n_groups < 2 * slots) {
     auto us = [&](int64_t n) {
@@ -211,8 +211,8 @@ static StreamCost stream_cost(int NT, int d, bool bf16) {
 // per head -- no adjacent rows -- and keeps one head per workgroup.
 // MD_HEADS_PER_WG (1 or 2) overrides, for measurement.
 static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64_t slots,
-                               int64_t whole, const StreamCost* cost, int64_t rows,
-                               int64_t tok_bytes) {
+                               int64_t whole, int64_t min_chunk, const StreamCost* cost,
+                               int64_t rows, int64_t tok_bytes) {
   const int forced = env_knob("MD_HEADS_PER_WG", 1, 2);
   if (a->num_kv_heads % 2) return 1;
   if (forced) return forced;
@@ -220,13 +220,13 @@ static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64
   const int64_t pairs = static_cast<int64_t>(a->num_seqs) * a->num_kv_heads / 2;
   if (pairs >= slots) return 2;
   int64_t n_chunks, chunk_len;
-  split_units(U, pairs, slots, whole, cost, 2 * rows, 2 * tok_bytes, a->head_dim, &n_chunks,
-              &chunk_len);
+  split_units(U, pairs, slots, whole, min_chunk, cost, 2 * rows, 2 * tok_bytes, a->head_dim,
+              &n_chunks, &chunk_len);
   return chunk_len >= kPairMinChunkTokens ? 2 : 1;
 }
 
 Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_cus,
-               int64_t whole) {
+               bool plain) {
   Plan p;
   const int L = a->q_len;
   p.G = a->num_q_heads / a->num_kv_heads;
@@ -254,20 +254,23 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // units of 427 tokens through the binding: 17.4 us whole, 17.9 split).  A
   // listed draft keeps lists of up to kWholeList positions whole, so that they
   // need no workspace.
-  whole = std::max(whole, mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
+  const int64_t min_chunk = plain ? kPlainChunkTokens : kMinChunkTokens;
+  const int64_t whole = std::max<int64_t>(
+      plain ? kPlainChunkTokens : 0,
+      mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
   const bool bf16 = a->dtype == MD_BF16;
   const StreamCost sc = stream_cost(p.NT, a->head_dim, bf16);
-  const StreamCost* cost = env_knob("MD_SLOTS_SCALE", 2, 4) ? nullptr : &sc;
+  const StreamCost* cost = plain || env_knob("MD_SLOTS_SCALE", 2, 4) ? nullptr : &sc;
   const int64_t tok_bytes = int64_t{2} * a->head_dim * (bf16 ? 2 : 4);
-  p.hp = heads_per_workgroup(a, mode, U, slots, whole, cost, p.R, tok_bytes);
+  p.hp = heads_per_workgroup(a, mode, U, slots, whole, min_chunk, cost, p.R, tok_bytes);
   p.n_groups = p.n_units / p.hp;
   int64_t n_chunks, chunk_len;
   // Long ranges of groups that cover the device are the balanced verify's (or
   // longest-first's): one chunk.
   const int bal_min = bf16 ? kBalMinLen : kLptMinLen;
   if (p.n_groups >= slots && U >= bal_min) cost = nullptr;
-  split_units(U, p.n_groups, slots, whole, cost, p.hp * p.R, p.hp * tok_bytes, a->head_dim,
-              &n_chunks, &chunk_len);
+  split_units(U, p.n_groups, slots, whole, min_chunk, cost, p.hp * p.R, p.hp * tok_bytes,
+              a->head_dim, &n_chunks, &chunk_len);
   p.n_chunks = static_cast<int32_t>(n_chunks);
   p.chunk_len = static_cast<int32_t>(chunk_len);
   // Balanced verify: where the units alone fill the device and lengths may
@@ -322,11 +325,12 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus) {
   const Plan p = make_plan(a, mode, n_sink, window, num_cus);
-  if (p.n_chunks > 1 && p.U_max <= kSplitNeedsWorkspace &&
-      (!a->workspace || a->workspace_bytes < p.workspace_bytes ||
-       (reinterpret_cast<uintptr_t>(a->workspace) & 255u)))
-    return make_plan(a, mode, n_sink, window, num_cus, kSplitNeedsWorkspace);
-  return p;
+  if (p.n_chunks == 1) return p;
+  const size_t have = a->workspace && !(reinterpret_cast<uintptr_t>(a->workspace) & 255u)
+                          ? a->workspace_bytes : 0;
+  if (have >= p.workspace_bytes) return p;
+  const Plan q = make_plan(a, mode, n_sink, window, num_cus, true);
+  return q.workspace_bytes == 0 ? q : p;
 }
 
 namespace {

@@ -76,6 +76,18 @@ void plan_invariants(const md_attn_args& a, int mode, int n_sink, int window) {
     check(p.workspace_bytes <= md::kBalMaxWorkspace, "balanced workspace bound",
           static_cast<long long>(p.workspace_bytes));
   }
+  // Without a workspace a call is refused only where units that leave compute
+  // units idle are split, or for the balanced verify.
+  md_attn_args none = a;
+  none.workspace = nullptr;
+  const md::Plan bare = md::plan_call(&none, mode, n_sink, window, 256);
+  const md::Plan plain = md::make_plan(&a, mode, n_sink, window, 256, true);
+  if (!p.bal && !plain.bal) {
+    if (p.n_units >= 512 || p.U_max <= 1024)
+      check(bare.workspace_bytes == 0, "covering units run bare", p.n_units, p.U_max);
+    check((bare.workspace_bytes == 0) == (plain.workspace_bytes == 0 || p.n_chunks == 1),
+          "bare calls run the plain plan", bare.n_chunks, plain.n_chunks);
+  }
   if (p.n_chunks > 1 || p.bal)
     check(p.workspace_bytes >= p.counter_bytes + p.part_o_bytes + p.part_lse_bytes,
           "workspace parts", static_cast<long long>(p.workspace_bytes));

@@ -176,3 +176,29 @@ def test_splits_past_the_compute_units(case):
     say(f"[past-slots] {case[:4]} d={d} workspace {need} B")
     assert need > B * L * Hq * (d + 1) * 4, "the case must split its range"
     compare(*_call(oracle.VERIFY, c, None), *run_oracle(oracle.VERIFY, c), "bf16", str(case[:4]))
+
+
+@pytest.mark.parametrize("entry", ["bare", "noalloc"])
+def test_covering_units_without_a_workspace(entry):
+    """320 units cover the compute units by themselves: a split that only saves
+    time asks no caller for a workspace, and the entry point that allocates
+    nothing runs it unsplit too."""
+    import ctypes
+    lib = md.load_library()
+    B, Hkv, Hq, L, lens, d, page = PAST_SLOTS[0]
+    c = wl.make_case(B=B, q_len=L, Hq=Hq, Hkv=Hkv, d=d, kv_lens=lens, dtype="bf16", page_size=page,
+                     seed=750, device=DEV)
+    assert _need(oracle.VERIFY, c) > 0
+    out = torch.full_like(c["q"], float("nan"))
+    lse = torch.full(c["q"].shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    kw = dict(max_kv_len=c["max_kv_len"], page_table=c["page_table"], out=out, lse=lse)
+    say(f"[no workspace] {entry}")
+    if entry == "noalloc":
+        md.md_attn_noalloc(oracle.VERIFY, c["q"], c["k"], c["v"], c["kv_lens"], **kw)
+    else:
+        a = md.make_args(c["q"], c["k"], c["v"], c["kv_lens"], **kw)
+        st = torch.cuda.current_stream().cuda_stream
+        assert lib.md_verify_attn(ctypes.byref(a), st) == md.MD_OK
+    torch.cuda.synchronize()
+    compare(out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
+            *run_oracle(oracle.VERIFY, c), "bf16", f"no workspace, {entry}")

@@ -897,7 +897,9 @@ attn_partial_kernel(const AttnParams p) {
       float* op = p.part_o + prow * D + c0;
       *reinterpret_cast<f32x4*>(op) = f32x4{o8[0], o8[1], o8[2], o8[3]};
       *reinterpret_cast<f32x4*>(op + 4) = f32x4{o8[4], o8[5], o8[6], o8[7]};
-      if (c0 == 0) p.part_lse[prow] = lse;
+      // A NaN sum stays NaN: -inf would tell the merge that the part is empty,
+      // and a row with a NaN score would lose it.
+      if (c0 == 0) p.part_lse[prow] = Lt == Lt ? lse : Lt;
     }
   }
 
@@ -946,7 +948,10 @@ attn_partial_kernel(const AttnParams p) {
         const int i = r / p.G, h = (hk0 + hs) * p.G + r % p.G;
         const int64_t row_g = (static_cast<int64_t>(b) * L + i) * p.Hq + h;
         float mx = -INFINITY;
-        for (int k = 0; k < n_parts; ++k) mx = fmaxf(mx, p.part_lse[part_row(k, hs, r, row_g)]);
+        for (int k = 0; k < n_parts; ++k) {
+          const float l = p.part_lse[part_row(k, hs, r, row_g)];
+          mx = l > mx || l != l ? l : mx;  // a NaN part's row is NaN
+        }
         float o8[8];
         for (int j = 0; j < 8; ++j) o8[j] = 0.f;
         float lse = -INFINITY;
@@ -971,7 +976,7 @@ attn_partial_kernel(const AttnParams p) {
             }
           }
         }
-        store_out(row_g, c0, o8, lse);
+        store_out(row_g, c0, o8, lse == lse ? lse : -INFINITY);  // as an unsplit row
       }
     }
   }

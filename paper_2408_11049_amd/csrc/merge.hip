@@ -59,7 +59,7 @@ merge_lse_kernel(int n_parts, int64_t n_rows, const float* __restrict__ o_parts,
     }
     float mx = -INFINITY;
     for (int k = 0; k < kRegParts; ++k)
-      if (k < n_parts) mx = fmaxf(mx, lv[k]);
+      if (k < n_parts && (lv[k] > mx || lv[k] != lv[k])) mx = lv[k];  // a NaN part's row is NaN
     float acc[CPL];
     for (int j = 0; j < CPL; ++j) acc[j] = 0.f;
     float lse_r = -INFINITY;
@@ -86,7 +86,7 @@ merge_lse_kernel(int n_parts, int64_t n_rows, const float* __restrict__ o_parts,
       float* dst = static_cast<float*>(o) + row * D + lane * CPL;
       for (int j = 0; j < CPL; ++j) dst[j] = acc[j];
     }
-    if (lse && lane == 0) lse[row] = lse_r;
+    if (lse && lane == 0) lse[row] = lse_r == lse_r ? lse_r : -INFINITY;  // as an unsplit row
     return;
   }
 
@@ -180,7 +180,15 @@ merge_many_kernel(int n_parts, int64_t n_rows, const float* __restrict__ o_parts
       if (k0 + t >= n_parts) lv[t] = -INFINITY;
       mx = fmaxf(mx, lv[t]);
     }
-    if (mx == -INFINITY) continue;  // uniform over the wave
+    if (mx == -INFINITY) {  // uniform over the wave: empty parts, or NaN ones
+#pragma unroll
+      for (int t = 0; t < kRegParts; ++t) {
+        if (lv[t] == lv[t]) continue;
+        l = lv[t];
+        for (int j = 0; j < CPL; ++j) acc[j] = lv[t];
+      }
+      continue;
+    }
     const float f = __builtin_amdgcn_exp2f((m - mx) * kLog2e);
     l *= f;
     for (int j = 0; j < CPL; ++j) acc[j] *= f;

@@ -202,3 +202,22 @@ def test_covering_units_without_a_workspace(entry):
     torch.cuda.synchronize()
     compare(out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
             *run_oracle(oracle.VERIFY, c), "bf16", f"no workspace, {entry}")
+
+
+# Hkv, lens, position of the NaN key: merges of a few parts, of nine (the last
+# part alone in its wave) and of 32, and cut groups of the balanced verify.
+NAN_KEYS = [(1, [600], 599), (1, [600], 0), (1, [9 * 128], 9 * 128 - 1), (1, [4001], 2000),
+            (8, [4700 + 7 * i for i in range(64)], 4650)]
+
+
+@pytest.mark.parametrize("case", NAN_KEYS, ids=[f"nan{i}" for i in range(len(NAN_KEYS))])
+def test_nan_score_reaches_the_row(case):
+    """A NaN key makes its sequence's rows NaN (lse -inf), split or not."""
+    Hkv, lens, at = case
+    c = _case(len(lens), 1, 4 * Hkv, Hkv, lens, 0, 760)
+    assert _need(oracle.VERIFY, c) > 0
+    c["k"][0, at] = float("nan")
+    say(f"[nan key] {Hkv} heads, {len(lens)} sequences, at {at}")
+    o, lse = _call(oracle.VERIFY, c, None)
+    assert np.isnan(o[0]).all() and np.isneginf(lse[0]).all()
+    assert np.isfinite(o[1:]).all() and np.isfinite(lse[1:]).all()

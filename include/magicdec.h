@@ -142,11 +142,13 @@ typedef struct {
  * capacity) > 2^31 - 65, kv_stride_tok > 2^28 elements,
  * num_seqs * num_kv_heads > 2^31 - 1, num_seqs * q_len * num_q_heads >
  * 4 (2^31 - 1); MD_ERR_WORKSPACE when md_workspace_bytes() is nonzero for
- * these arguments and the workspace is missing, smaller or not 256-byte
- * aligned (which calls need one -- split ranges, the balanced verify --
- * depends on the sizes and the device, so size it for every new shape; ranges
- * of at most 1024 tokens, and outside the balanced verify units that cover the
- * compute units by themselves, run unsplit, more slowly, without one);
+ * these arguments and the workspace is missing, not 256-byte aligned or too
+ * small for every plan of the call (one smaller than md_workspace_bytes() may
+ * still hold a coarser split, which then runs).  Which calls need one -- split
+ * ranges, the balanced verify -- depends on the sizes and the device, so size
+ * it for every new shape; ranges of at most 1024 tokens, and outside the
+ * balanced verify units that cover the compute units by themselves, run
+ * unsplit, more slowly, without one;
  * MD_ERR_HIP.
  */
 int md_verify_attn(const md_attn_args* a, void* stream);
@@ -201,8 +203,8 @@ int md_merge_lse(int32_t n_parts, int64_t n_rows, int32_t head_dim, int32_t out_
                  void* stream);
 
 /*
- * Workspace bytes an attention call with these arguments needs (0 when the
- * call runs as a single pass).  A split-range call keeps there, per head
+ * Workspace bytes an attention call with these arguments needs to run its best
+ * plan (0 when that is a single pass).  A split-range call keeps there, per head
  * group, an arrival counter tagged with the call, then every chunk's partial
  * O and lse (the split-KV identity, Sec. 2).  A balanced verify (batches of
  * 2..256 long sequences whose head groups number at most two per compute

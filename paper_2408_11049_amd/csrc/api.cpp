@@ -319,14 +319,13 @@ size_t md_workspace_bytes(const md_attn_args* a, int32_t mode, int32_t n_sink, i
   if (mode != MD_MODE_VERIFY && mode != MD_MODE_DRAFT) return 0;
   if (mode == MD_MODE_DRAFT && (n_sink < 0 || window < 1 || window > md::kMaxPosition)) return 0;
   if (md::check_attn_sizes(a) != MD_OK) return 0;
-  return md::make_plan(a, mode, n_sink, window, md::device_cu_count()).workspace_bytes;
+  return md::workspace_need(a, mode, n_sink, window, md::device_cu_count());
 }
 
 size_t md_workspace_bytes_indexed(const md_attn_args* a, int32_t idx_stride) {
   if (!a || idx_stride < 1 || idx_stride > md::kMaxPosition) return 0;
   if (md::check_attn_sizes(a) != MD_OK) return 0;
-  return md::make_plan(a, MD_MODE_DRAFT_INDEXED, 0, idx_stride, md::device_cu_count())
-      .workspace_bytes;
+  return md::workspace_need(a, MD_MODE_DRAFT_INDEXED, 0, idx_stride, md::device_cu_count());
 }
 
 int md_snapkv_votes(const md_snapkv_args* a, void* stream) {

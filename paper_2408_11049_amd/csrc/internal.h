@@ -111,8 +111,13 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
                bool plain = false);
 
 // The decomposition a call runs: make_plan, or the plain plan when the caller's
-// workspace does not serve the split and that needs none.
+// workspace serves that one only.
 Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus);
+
+// What md_workspace_bytes answers: enough for either plan, so that a buffer
+// sized for the longest cache also holds the plain plan of a shorter one (the
+// need of make_plan's own choice can fall as the range grows).
+size_t workspace_need(const md_attn_args* a, int mode, int n_sink, int window, int num_cus);
 
 // SnapKV selection: validation and the chunking of its two passes.
 constexpr int kSnapkvMaxRows = 256;  // G * n_obs

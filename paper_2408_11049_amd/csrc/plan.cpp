@@ -325,12 +325,17 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
 
 Plan plan_call(const md_attn_args* a, int mode, int n_sink, int window, int num_cus) {
   const Plan p = make_plan(a, mode, n_sink, window, num_cus);
-  if (p.n_chunks == 1) return p;
   const size_t have = a->workspace && !(reinterpret_cast<uintptr_t>(a->workspace) & 255u)
                           ? a->workspace_bytes : 0;
   if (have >= p.workspace_bytes) return p;
   const Plan q = make_plan(a, mode, n_sink, window, num_cus, true);
-  return q.workspace_bytes == 0 ? q : p;
+  return have >= q.workspace_bytes ? q : p;
+}
+
+size_t workspace_need(const md_attn_args* a, int mode, int n_sink, int window, int num_cus) {
+  const size_t need = make_plan(a, mode, n_sink, window, num_cus).workspace_bytes;
+  if (!need) return 0;
+  return std::max(need, make_plan(a, mode, n_sink, window, num_cus, true).workspace_bytes);
 }
 
 namespace {

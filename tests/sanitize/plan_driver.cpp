@@ -59,6 +59,45 @@ md_attn_args good_args(int B, int L, int Hq, int Hkv, int d, int64_t S, int page
 }
 
 int g_bal_plans = 0;
+int g_between = 0;  // shapes whose plain plan needs less than the call's first choice
+
+// Smaller workspaces than the first choice's: the call runs a plan that fits
+// whenever one of the two does, and a buffer sized for the longest cache serves
+// every shorter one that the plain plan's size served.
+void workspace_between(const md_attn_args& a, int mode, int n_sink, int window) {
+  const md::Plan p = md::make_plan(&a, mode, n_sink, window, 256);
+  const md::Plan q = md::make_plan(&a, mode, n_sink, window, 256, true);
+  const size_t need = md::workspace_need(&a, mode, n_sink, window, 256);
+  check((need == 0) == (p.workspace_bytes == 0) && need >= p.workspace_bytes, "need covers the plan",
+        static_cast<long long>(need), static_cast<long long>(p.workspace_bytes));
+  g_between += q.workspace_bytes && q.workspace_bytes < p.workspace_bytes;
+  const size_t least = p.workspace_bytes < q.workspace_bytes ? p.workspace_bytes : q.workspace_bytes;
+  for (size_t have : {least, q.workspace_bytes, p.workspace_bytes, (least + need) / 2, need}) {
+    md_attn_args b = a;
+    b.workspace_bytes = have;
+    check(md::plan_call(&b, mode, n_sink, window, 256).workspace_bytes <= have || have < least,
+          "a plan that fits the workspace is run", static_cast<long long>(have),
+          static_cast<long long>(least));
+    const int st = md::validate_attn(&b, mode, n_sink, window);
+    check((st == MD_OK) == (have >= least), "workspace between the two plans", st,
+          static_cast<long long>(have));
+  }
+  if (least) {
+    md_attn_args b = a;
+    b.workspace_bytes = least - 1;
+    check(md::validate_attn(&b, mode, n_sink, window) == MD_ERR_WORKSPACE, "too small a workspace",
+          static_cast<long long>(least));
+  }
+  for (int64_t S = a.max_kv_len; need && S >= a.q_len; S = S * 7 / 8) {
+    md_attn_args b = a;
+    b.max_kv_len = static_cast<int32_t>(S);
+    const size_t plain = md::make_plan(&b, mode, n_sink, window, 256, true).workspace_bytes;
+    b.workspace_bytes = need;
+    if (plain <= q.workspace_bytes)
+      check(md::plan_call(&b, mode, n_sink, window, 256).workspace_bytes <= need,
+            "the longest cache's workspace serves a shorter one", a.max_kv_len, S);
+  }
+}
 
 void plan_invariants(const md_attn_args& a, int mode, int n_sink, int window) {
   const md::Plan p = md::make_plan(&a, mode, n_sink, window, 256);
@@ -165,6 +204,7 @@ int main() {
               const int window = mode == MD_MODE_VERIFY ? 1 : static_cast<int>(S < 2048 ? S : 2048);
               if (md::validate_attn(&a, mode, 64, window) != MD_OK) continue;
               plan_invariants(a, mode, 64, window);
+              if (pass == 0) workspace_between(a, mode, 64, window);
             }
           }
         }
@@ -181,6 +221,8 @@ int main() {
         bal_per_pass[2], bal_per_pass[3]);
   printf("balanced plans per pass: %d %d %d %d\n", bal_per_pass[0], bal_per_pass[1],
          bal_per_pass[2], bal_per_pass[3]);
+
+  check(g_between > 0, "sweep reaches workspaces between the two plans", g_between);
 
   // ---- SnapKV, acceptance and cache validators over edge sizes
   for (int32_t n : {0, 1, 32, 256, INT32_MAX}) {

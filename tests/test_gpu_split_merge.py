@@ -221,3 +221,27 @@ def test_nan_score_reaches_the_row(case):
     o, lse = _call(oracle.VERIFY, c, None)
     assert np.isnan(o[0]).all() and np.isneginf(lse[0]).all()
     assert np.isfinite(o[1:]).all() and np.isfinite(lse[1:]).all()
+
+
+@pytest.mark.parametrize("share", ["sixth", "longer_cache"])
+def test_workspace_between_plans(share):
+    """One sequence of 16384 tokens: a workspace that holds the coarse split but
+    not the finer one runs the coarse one, as does the workspace of a longer
+    cache, whose own need is the smaller of the two."""
+    import ctypes
+    lib = md.load_library()
+    c = _case(1, 1, 8, 2, [16384], 16, 770)
+    need = _need(oracle.VERIFY, c)
+    nbytes = need // 6 if share == "sixth" else _need(
+        oracle.VERIFY, _case(1, 1, 8, 2, [24000], 16, 771))
+    assert nbytes < need
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    out = torch.full_like(c["q"], float("nan"))
+    lse = torch.full(c["q"].shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    a = md.make_args(c["q"], c["k"], c["v"], c["kv_lens"], max_kv_len=c["max_kv_len"],
+                     page_table=c["page_table"], out=out, lse=lse, workspace=ws)
+    say(f"[workspace between] {nbytes} of {need} B")
+    assert lib.md_verify_attn(ctypes.byref(a), torch.cuda.current_stream().cuda_stream) == md.MD_OK
+    torch.cuda.synchronize()
+    compare(out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
+            *run_oracle(oracle.VERIFY, c), "bf16", f"{nbytes} of {need} B")

@@ -146,9 +146,11 @@ typedef struct {
  * small for every plan of the call (one smaller than md_workspace_bytes() may
  * still hold a coarser split, which then runs).  Which calls need one -- split
  * ranges, the balanced verify -- depends on the sizes and the device, so size
- * it for every new shape; ranges of at most 1024 tokens, and outside the
- * balanced verify units that cover the compute units by themselves, run
- * unsplit, more slowly, without one;
+ * it for every new shape.  Without one, ranges of at most 1024 tokens run
+ * unsplit, more slowly, and so do, outside the balanced verify, calls whose
+ * num_seqs * num_kv_heads is at least the device's compute units (twice them
+ * when num_kv_heads is even: a workgroup may take a pair of heads, and fewer
+ * pairs than compute units are split);
  * MD_ERR_HIP.
  */
 int md_verify_attn(const md_attn_args* a, void* stream);
@@ -242,7 +244,7 @@ size_t md_workspace_bytes_indexed(const md_attn_args* a, int32_t idx_stride);
  *   - All calls on one GPU share its buffer, which keeps the last call's
  *     contents; nothing in it needs clearing (the counters carry a per-call
  *     tag).  Calls that md_verify_attn or md_draft_attn would run without a
- *     workspace run unsplit and leave it alone.  Others that can overlap in
+ *     workspace (see there) run unsplit and leave it alone.  Others that can overlap in
  *     time on one GPU (other streams, other threads) race on it and give
  *     wrong results: serialise them.
  *   - `stream` (NULL: the null stream) must belong to the current device.

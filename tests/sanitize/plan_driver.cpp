@@ -59,6 +59,7 @@ md_attn_args good_args(int B, int L, int Hq, int Hkv, int d, int64_t S, int page
 }
 
 int g_bal_plans = 0;
+int g_pairs_refused = 0;  // units cover the device, their pairs do not: split, refused bare
 int g_between = 0;  // shapes whose plain plan needs less than the call's first choice
 
 // Smaller workspaces than the first choice's: the call runs a plan that fits
@@ -115,17 +116,19 @@ void plan_invariants(const md_attn_args& a, int mode, int n_sink, int window) {
     check(p.workspace_bytes <= md::kBalMaxWorkspace, "balanced workspace bound",
           static_cast<long long>(p.workspace_bytes));
   }
-  // Without a workspace a call is refused only where units that leave compute
-  // units idle are split, or for the balanced verify.
+  // Without a workspace a call is refused only where fewer units (twice the
+  // compute units, when heads may pair) are split, or for the balanced verify.
+  const int64_t covering = a.num_kv_heads % 2 ? 256 : 512;
   md_attn_args none = a;
   none.workspace = nullptr;
   const md::Plan bare = md::plan_call(&none, mode, n_sink, window, 256);
   const md::Plan plain = md::make_plan(&a, mode, n_sink, window, 256, true);
   if (!p.bal && !plain.bal) {
-    if (p.n_units >= 512 || p.U_max <= 1024)
+    if (p.n_units >= covering || p.U_max <= 1024)
       check(bare.workspace_bytes == 0, "covering units run bare", p.n_units, p.U_max);
     check((bare.workspace_bytes == 0) == (plain.workspace_bytes == 0 || p.n_chunks == 1),
           "bare calls run the plain plan", bare.n_chunks, plain.n_chunks);
+    g_pairs_refused += p.n_units >= 256 && p.n_units < covering && bare.workspace_bytes != 0;
   }
   if (p.n_chunks > 1 || p.bal)
     check(p.workspace_bytes >= p.counter_bytes + p.part_o_bytes + p.part_lse_bytes,
@@ -177,7 +180,7 @@ int main() {
   // ---- extreme but valid sizes: plans stay within their invariants
   const int64_t lens[] = {1, 5, 31, 32, 33, 1023, 1024, 4096, 8192, 32768, 131072, 1 << 20,
                           static_cast<int64_t>(md::kMaxPosition)};
-  const int batches[] = {1, 2, 3, 16, 64, 255, 256, 4096, 1 << 16};
+  const int batches[] = {1, 2, 3, 16, 64, 128, 255, 256, 4096, 1 << 16};
   const int heads[][2] = {{4, 1}, {8, 2}, {32, 8}, {64, 8}, {16, 16}, {64, 1}};
   // The sweep runs with the default plan choice, then with the balanced
   // verify forced wherever allowed, and with its range count at the knob's
@@ -222,6 +225,7 @@ int main() {
   printf("balanced plans per pass: %d %d %d %d\n", bal_per_pass[0], bal_per_pass[1],
          bal_per_pass[2], bal_per_pass[3]);
 
+  check(g_pairs_refused > 0, "sweep reaches split head pairs", g_pairs_refused);
   check(g_between > 0, "sweep reaches workspaces between the two plans", g_between);
 
   // ---- SnapKV, acceptance and cache validators over edge sizes

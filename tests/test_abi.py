@@ -226,7 +226,12 @@ def test_workspace_required_and_checked(lib):
     need = lib.md_workspace_bytes(ctypes.byref(a), md.MD_MODE_VERIFY, 0, 1)
     assert need > 0
     assert lib.md_verify_attn(ctypes.byref(a), None) == md.MD_ERR_WORKSPACE
-    a.workspace, a.workspace_bytes = FAKE, need - 1
+    # The least any plan of the call takes: 64 chunks of 1024 tokens, their
+    # partial O and lse and one counter.
+    rows, up = a.q_len * 4, lambda x: (x + 255) // 256 * 256
+    least = up(8) + up(64 * rows * 128 * 4) + up(64 * rows * 4)
+    assert least < need
+    a.workspace, a.workspace_bytes = FAKE, least - 1
     assert lib.md_verify_attn(ctypes.byref(a), None) == md.MD_ERR_WORKSPACE
     a.workspace, a.workspace_bytes = FAKE + 16, need
     assert lib.md_verify_attn(ctypes.byref(a), None) == md.MD_ERR_WORKSPACE  # not 256-aligned

@@ -123,16 +123,16 @@ struct StreamCost {
   double wg_rate;    // bytes/us of one workgroup
   int resident;      // workgroups a compute unit holds
 };
-static double launch_us(const StreamCost& c, int64_t wgs, double bytes, int64_t cus) {
-  constexpr double kChipRate = 7.0e6, kCuRate = 34.0e3;
-  const int64_t round = cus * c.resident;
+static double launch_us(const StreamCost& c, int32_t wgs, double bytes, int32_t cus) {
+  constexpr double kChipUs = 1.0 / 7.0e6, kCuUs = 1.0 / 34.0e3;  // us per byte
+  const int32_t round = cus * c.resident;
+  const double slowest = 1.0 / c.wg_rate;
   double us = 0.0;
-  for (int64_t left = wgs; left > 0; left -= round) {
-    const int64_t w = std::min(left, round);
-    const double per_cu = kCuRate / static_cast<double>(ceil_div(w, cus));
+  for (int32_t left = wgs; left > 0; left -= round) {
+    const int32_t w = std::min(left, round);
+    const int32_t per_cu = w <= cus ? 1 : (w + cus - 1) / cus;
     // Later rounds start as workgroups of the round before finish.
-    const double chip = kChipRate / static_cast<double>(w);
-    us += c.start + bytes / std::min(c.wg_rate, std::min(per_cu, chip));
+    us += c.start + bytes * std::max(slowest, std::max(per_cu * kCuUs, w * kChipUs));
   }
   return us;
 }
@@ -153,20 +153,32 @@ static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whol
   const int64_t cap = U <= whole ? 1 : ceil_div(U, min_chunk);
   if (n_groups > 0 && n_groups < slots) n_chunks = std::min(ceil_div(slots, n_groups), cap);
   if (cost && n_groups > 0 && cap > 1 && n_groups < 2 * slots) {
-    auto us = [&](int64_t n) {
-      const double parts = n > 1 ? 2.0 * n * n_groups * group_rows * (d + 1) * 4 : 0.0;
-      const double chunk = static_cast<double>(ceil_div(ceil_div(U, n), kTile) * kTile);
-      return launch_us(*cost, n * n_groups, chunk * tok_bytes, slots) +
-             (n > 1 ? kMergeUs + parts / 6.0e6 : 0.0);
+    // In tiles and 32 bits: a division of 64 would cost as much as the rest.
+    const uint32_t tiles = static_cast<uint32_t>(ceil_div(U, kTile));
+    const int32_t g = static_cast<int32_t>(n_groups), cus = static_cast<int32_t>(slots);
+    const double tile_bytes = static_cast<double>(kTile * tok_bytes);
+    const double part_bytes = static_cast<double>(n_groups * group_rows * (d + 1) * 4);
+    auto us = [&](uint32_t n, uint32_t len) {
+      return launch_us(*cost, static_cast<int32_t>(n) * g, len * tile_bytes, cus) +
+             (n > 1 ? kMergeUs + n * part_bytes * (2.0 / 6.0e6) : 0.0);
     };
-    double best = us(n_chunks) * 0.95;
-    for (int64_t n = 1; n <= cap && n * n_groups <= 4 * slots; ++n) {
-      if (n * n_groups * group_rows * (d + 1) * 4 > kSplitMaxPartials) break;
-      const double t = us(n);
+    const uint32_t first = static_cast<uint32_t>(n_chunks);
+    double best = us(first, (tiles + first - 1) / first) * 0.95;
+    const uint32_t last = static_cast<uint32_t>(std::min(
+        std::min(cap, 4 * slots / n_groups),
+        std::max<int64_t>(1, static_cast<int64_t>(kSplitMaxPartials / part_bytes))));
+    const uint32_t half = static_cast<uint32_t>(cus / (2 * g));
+    for (uint32_t n = 1; n <= last;) {
+      const uint32_t len = (tiles + n - 1) / n;
+      const double t = us(n, len);
       if (t < best) {
         best = t;
         n_chunks = n;
       }
+      if (len <= 1) break;
+      // The next count that shortens the chunk (those between cost no less),
+      // from a split over half of the compute units on.
+      n = std::max((tiles + len - 2) / (len - 1), half);
     }
   }
   int64_t chunk_len = ceil_div(ceil_div(U, n_chunks), kTile) * kTile;
@@ -219,6 +231,10 @@ static int heads_per_workgroup(const md_attn_args* a, int mode, int64_t U, int64
   if (mode == MD_MODE_DRAFT_INDEXED) return 1;
   const int64_t pairs = static_cast<int64_t>(a->num_seqs) * a->num_kv_heads / 2;
   if (pairs >= slots) return 2;
+  // No chunk is as long, or such chunks use less than half of the device.
+  if (U <= kPairMinChunkTokens - kTile ||
+      ceil_div(U, kPairMinChunkTokens - kTile) * pairs < slots / 2)
+    return 1;
   int64_t n_chunks, chunk_len;
   split_units(U, pairs, slots, whole, min_chunk, cost, 2 * rows, 2 * tok_bytes, a->head_dim,
               &n_chunks, &chunk_len);

@@ -611,3 +611,26 @@ def test_noalloc_refuses_before_any_hip_call(lib, monkeypatch):
     need = lib.md_workspace_bytes(ctypes.byref(a), 0, 0, 1)
     assert need > md.MD_NOALLOC_SCRATCH_BYTES
     assert lib.md_attn_noalloc(ctypes.byref(a), 0, 0, 1, None) == md.MD_ERR_WORKSPACE
+
+
+def test_planning_stays_cheap(lib):
+    """A call plans twice (the size query, then the call), so planning a long
+    range of few KV heads, which has the most splits to choose from, costs no
+    more than a few times a plan without a choice (best of many repeats)."""
+    import time
+
+    def best_us(B, Hkv, S):
+        a = good_args(num_seqs=B, num_q_heads=4 * Hkv, num_kv_heads=Hkv, q_len=1, max_kv_len=S,
+                      max_pages_per_seq=-(-S // 16), num_pages=B * -(-S // 16))
+        ref, best = ctypes.byref(a), float("inf")
+        for _ in range(30):
+            t = time.perf_counter()
+            for _ in range(100):
+                lib.md_workspace_bytes(ref, md.MD_MODE_VERIFY, 0, 1)
+            best = min(best, (time.perf_counter() - t) * 1e4)
+        return best
+
+    base = best_us(64, 8, 256)
+    for B, Hkv in ((1, 1), (1, 2), (1, 8), (3, 2)):
+        t = best_us(B, Hkv, 131072)
+        assert t < 5 * base, f"{B} x {Hkv} heads: {t:.2f} us a plan, {base:.2f} without a choice"

@@ -297,7 +297,9 @@ typedef struct {
  * MD_ERR_INVALID_ARG for NULL or misaligned pointers, bad sizes, a votes
  * stride below max_prompt_len - n_obs, max_prompt_len < n_obs;
  * MD_ERR_UNSUPPORTED for head_dim not in {64,128}, G * n_obs > 256 or
- * num_seqs * num_kv_heads > 2^31 - 1; MD_ERR_WORKSPACE; MD_ERR_HIP. */
+ * num_seqs * num_kv_heads > 2^31 - 1; MD_ERR_WORKSPACE (missing, misaligned,
+ * or too small for the coarsest cut of the prompts too, which runs where the
+ * best one does not fit); MD_ERR_HIP. */
 int md_snapkv_votes(const md_snapkv_args* a, void* stream);
 size_t md_snapkv_workspace_bytes(const md_snapkv_args* a);
 

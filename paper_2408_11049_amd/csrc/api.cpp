@@ -332,7 +332,7 @@ int md_snapkv_votes(const md_snapkv_args* a, void* stream) {
   const int st = md::validate_snapkv(a);
   if (st != MD_OK) return st;
   if (a->num_seqs == 0) return MD_OK;
-  const md::SnapkvPlan pl = md::make_snapkv_plan(a, md::device_cu_count());
+  const md::SnapkvPlan pl = md::snapkv_plan_call(a, md::device_cu_count());
   md::SnapkvParams p{};
   p.q = a->q_obs;
   p.k = a->k;
@@ -377,7 +377,7 @@ size_t md_snapkv_workspace_bytes(const md_snapkv_args* a) {
       a->num_q_heads % a->num_kv_heads || a->max_prompt_len < a->n_obs ||
       static_cast<int64_t>(a->num_seqs) * a->num_kv_heads > INT32_MAX)
     return 0;
-  return md::make_snapkv_plan(a, md::device_cu_count()).workspace_bytes;
+  return md::snapkv_workspace_need(a, md::device_cu_count());
 }
 
 int md_snapkv_select(int32_t num_seqs, int32_t num_kv_heads, const float* votes,

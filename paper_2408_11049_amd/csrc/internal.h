@@ -132,7 +132,11 @@ struct SnapkvPlan {
   size_t workspace_bytes = 0;
 };
 int validate_snapkv(const md_snapkv_args* a);
-SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus);
+// A plain plan cuts the prompts coarsely, for less workspace; snapkv_plan_call
+// and snapkv_workspace_need are to it what plan_call and workspace_need are.
+SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus, bool plain = false);
+SnapkvPlan snapkv_plan_call(const md_snapkv_args* a, int num_cus);
+size_t snapkv_workspace_need(const md_snapkv_args* a, int num_cus);
 
 // Greedy acceptance: rows = B * L logits rows, each cut into n_chunks chunks
 // of chunk_len elements (a multiple of 8; every chunk non-empty), one

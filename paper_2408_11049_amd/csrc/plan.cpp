@@ -402,6 +402,18 @@ void split_range(int64_t U, int64_t n_units, const PassCost& cost, int64_t cus,
   *chunk_len_out = static_cast<int32_t>(chunk_len);
 }
 
+// The chunks of a plain plan: enough for wg_per_cu workgroups per compute unit
+// twice over, of at least kPlainChunkTokens keys.
+void split_range_plain(int64_t U, int64_t n_units, int64_t wgs, int32_t* n_chunks_out,
+                       int32_t* chunk_len_out) {
+  int64_t n = 1;
+  if (n_units > 0 && n_units < 2 * wgs)
+    n = std::max<int64_t>(1, std::min(ceil_div(2 * wgs, n_units), ceil_div(U, kPlainChunkTokens)));
+  const int64_t chunk_len = ceil_div(ceil_div(U > 0 ? U : 1, n), kTile) * kTile;
+  *n_chunks_out = static_cast<int32_t>(ceil_div(U > 0 ? U : 1, chunk_len));
+  *chunk_len_out = static_cast<int32_t>(chunk_len);
+}
+
 // key_us: the scores of a key (0.013 us at 128 rows in bf16, 0.107 in fp32,
 // d = 128) or its bytes, whichever takes longer.  start_us grows with the rows
 // of Q a workgroup loads: 50 fp32 units of 256 rows take 258 us in 250
@@ -459,28 +471,46 @@ int validate_snapkv(const md_snapkv_args* a) {
   if (a->kv_stride_blk % per16 || a->kv_stride_tok % per16 || a->kv_stride_head % per16)
     return MD_ERR_INVALID_ARG;
   if (a->num_kv_heads > 1 && a->kv_stride_head < a->head_dim) return MD_ERR_INVALID_ARG;
-  const SnapkvPlan pl = make_snapkv_plan(a, device_cu_count());
+  const SnapkvPlan pl = snapkv_plan_call(a, device_cu_count());
   if (!a->workspace || a->workspace_bytes < pl.workspace_bytes ||
       (reinterpret_cast<uintptr_t>(a->workspace) & 255u))
     return MD_ERR_WORKSPACE;
   return MD_OK;
 }
 
-SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus) {
+SnapkvPlan make_snapkv_plan(const md_snapkv_args* a, int num_cus, bool plain) {
   SnapkvPlan p;
   p.G = a->num_q_heads / a->num_kv_heads;
   p.R = p.G * a->n_obs;
   p.TW = p.R <= 64 ? 1 : (p.R <= 128 ? 2 : 4);
   p.n_units = a->num_seqs * a->num_kv_heads;
   const int64_t cus = num_cus > 0 ? num_cus : 256;
-  const PassCost cost = pass_cost(p.R, a->head_dim, a->dtype == MD_F32);
-  split_range(a->max_prompt_len, p.n_units, cost, cus, &p.n_chunks_stats, &p.chunk_len_stats);
-  split_range(a->max_prompt_len - a->n_obs, p.n_units, cost, cus, &p.n_chunks_votes,
-              &p.chunk_len_votes);
+  const int64_t U = a->max_prompt_len, U_votes = U - a->n_obs;
+  if (plain) {
+    const int64_t wgs = cus * (p.TW == 1 ? 2 : 8);
+    split_range_plain(U, p.n_units, wgs, &p.n_chunks_stats, &p.chunk_len_stats);
+    split_range_plain(U_votes, p.n_units, wgs, &p.n_chunks_votes, &p.chunk_len_votes);
+  } else {
+    const PassCost cost = pass_cost(p.R, a->head_dim, a->dtype == MD_F32);
+    split_range(U, p.n_units, cost, cus, &p.n_chunks_stats, &p.chunk_len_stats);
+    split_range(U_votes, p.n_units, cost, cus, &p.n_chunks_votes, &p.chunk_len_votes);
+  }
   p.part_bytes = align_up(static_cast<size_t>(p.n_units) * p.n_chunks_stats * p.R * 4, 256);
   p.lse_bytes = align_up(static_cast<size_t>(p.n_units) * p.R * 4, 256);
   p.workspace_bytes = 2 * p.part_bytes + p.lse_bytes;
   return p;
+}
+
+SnapkvPlan snapkv_plan_call(const md_snapkv_args* a, int num_cus) {
+  const SnapkvPlan p = make_snapkv_plan(a, num_cus);
+  if (a->workspace_bytes >= p.workspace_bytes) return p;
+  const SnapkvPlan q = make_snapkv_plan(a, num_cus, true);
+  return a->workspace_bytes >= q.workspace_bytes ? q : p;
+}
+
+size_t snapkv_workspace_need(const md_snapkv_args* a, int num_cus) {
+  return std::max(make_snapkv_plan(a, num_cus).workspace_bytes,
+                  make_snapkv_plan(a, num_cus, true).workspace_bytes);
 }
 
 int validate_accept(int32_t num_seqs, int32_t n_draft, int32_t vocab, int32_t dtype) {

@@ -253,6 +253,47 @@ int main() {
       check(sp.n_chunks_stats >= 1 && sp.n_chunks_votes >= 1, "snapkv chunks");
     }
   }
+  // A votes workspace between the coarse cut's need and the best one's: the
+  // call's plan fits it, and one sized for long prompts serves shorter ones.
+  int between = 0;
+  for (int32_t B : {1, 2, 4, 33, 64})
+    for (int32_t n_obs : {8, 32})
+      for (int32_t G : {1, 2, 4, 8})
+        for (int32_t dt : {MD_BF16, MD_F32})
+          for (int32_t S : {200, 1000, 4001, 12000, 32768}) {
+            md_snapkv_args s{};
+            s.num_seqs = B;
+            s.n_obs = n_obs;
+            s.num_q_heads = 8 * G;
+            s.num_kv_heads = 8;
+            s.head_dim = 128;
+            s.dtype = dt;
+            s.q_obs = s.k = kFake;
+            s.kv_stride_head = 128;
+            s.kv_stride_tok = 1024;
+            s.kv_stride_blk = int64_t{1024} * S;
+            s.prompt_lens = reinterpret_cast<const int32_t*>(kFake);
+            s.max_prompt_len = s.votes_stride = S;
+            s.votes = reinterpret_cast<float*>(kFake);
+            s.workspace = kFake;
+            const size_t p = md::make_snapkv_plan(&s, 256).workspace_bytes;
+            const size_t q = md::make_snapkv_plan(&s, 256, true).workspace_bytes;
+            const size_t need = md::snapkv_workspace_need(&s, 256), least = p < q ? p : q;
+            between += q < p;
+            check(need >= p, "votes need", static_cast<long long>(need));
+            for (size_t have : {least - 1, least, (least + need) / 2, need}) {
+              s.workspace_bytes = have;
+              check((md::validate_snapkv(&s) == MD_OK) == (have >= least), "votes workspace", B, S);
+              check(have < least || md::snapkv_plan_call(&s, 256).workspace_bytes <= have,
+                    "votes plan fits the workspace", B, S);
+            }
+            s.max_prompt_len = S * 3 / 4;
+            s.workspace_bytes = need;
+            check(md::make_snapkv_plan(&s, 256, true).workspace_bytes > q ||
+                      md::validate_snapkv(&s) == MD_OK,
+                  "the longest prompts' workspace serves shorter ones", B, S);
+          }
+  check(between > 0, "votes workspaces between the two plans", between);
   for (int32_t B : {0, 1, 64, 1 << 20})
     for (int32_t nd : {-1, 0, 4, 1023, 1024})
       for (int32_t vocab : {0, 1, 8, 128256, 1 << 30, (1 << 30) + 1, INT32_MAX}) {

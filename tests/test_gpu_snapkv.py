@@ -107,6 +107,23 @@ def test_votes_wave_grids(G, n_obs, d):
                                    lens, "bf16", ps))
 
 
+def test_votes_with_a_coarse_cuts_workspace():
+    """A workspace an eighth of the query's answer holds the coarse cut of one
+    prompt; its votes are those of the best cut to the rounding of fp32 sums."""
+    c = wl.make_case(B=1, q_len=1, Hq=32, Hkv=8, d=128, kv_lens=[4001], dtype="bf16", page_size=16,
+                     seed=905, device=DEV)
+    q = torch.randn((1, 32, 32, 128), device=DEV, generator=torch.Generator(DEV).manual_seed(9))
+    q = q.to(torch.bfloat16)
+    kw = dict(max_prompt_len=4001, page_table=c["page_table"])
+    need = md.md_snapkv_workspace_bytes(q, c["k"], c["kv_lens"], **kw)
+    say(f"[votes, coarse cut] {need // 6} of {need} B")
+    full = md.md_snapkv_votes(q, c["k"], c["kv_lens"], **kw)
+    coarse = md.md_snapkv_votes(q, c["k"], c["kv_lens"], workspace=torch.empty(
+        need // 6, dtype=torch.uint8, device=DEV), **kw)
+    # A row's lse moves by the rounding of its sums: 4001 terms of 2^-24 at most.
+    assert torch.allclose(full, coarse, rtol=4001 * 2.0 ** -24, atol=0)
+
+
 # rows, stride, n_obs, budget, pool, prompt lens (per sequence), Hkv
 SELECT = [
     (3, 500, 32, 64, 5, [532, 300, 40], 2),

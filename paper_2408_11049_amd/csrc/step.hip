@@ -141,18 +141,21 @@ __global__ void __launch_bounds__(256) kv_gather_kernel(const GatherParams p) {
 // sequence, sequences, K/V), each sequence's items in the order above, so an
 // item's (list slot, kv head, vector) are shifts and masks of its index
 // rather than 64-bit divisions, and only the listed rows are visited.  Each
-// thread takes kGatherItems items per iteration and issues their list reads,
-// then their row loads, then their stores, so the dependent reads of one item
-// (list entry, page id, row) overlap those of the others.  Bounded by HBM, read
-// and write mixed (a plain copy moves 4.8 TB/s here); the rows are written
-// around the caches, since nothing reads them before the next draft step.  2049
-// rows of 8 heads of 32 sequences (537 MB): 109 us with cached stores and four
-// items, 102 with these stores, 101 with three items, 110 with two, 124 with one.
-constexpr int kGatherItems = 3;  // items per thread and iteration
+// thread takes several items per iteration and issues their list reads, then
+// their row loads, then their stores, so the dependent reads of one item (list
+// entry, page id, row) overlap those of the others: three items into contiguous
+// rows, four into pages.  Bounded by HBM, read and write mixed (a plain copy
+// moves 4.8 TB/s).  2049 rows of 8 heads, pages to contiguous rows, three / four
+// items: after a 1 GiB read 64 sequences 190.6 / 192.1 us; call after call 32
+// sequences 94.6 / 96.7, 64 sequences 208 / 216; into pages 257 / 239.  Stores
+// around the caches instead: 203.8, 102, 201, and into pages 254 / 234; they win
+// only where calls follow each other and the rows outgrow the last-level cache.
+template <bool DST_PAGED>
+constexpr int kGatherItems = DST_PAGED ? 4 : 3;  // items per thread and iteration
 
 template <bool SRC_PAGED, bool DST_PAGED>
 __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams p) {
-  constexpr int U = kGatherItems;  // their loads overlap
+  constexpr int U = kGatherItems<DST_PAGED>;  // their loads overlap
   const bool is_v = blockIdx.z != 0;
   const int vshift = p.vec_shift, hshift = p.head_shift;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
@@ -197,8 +200,7 @@ __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams 
         if (!in[u] || !cache_row<DST_PAGED>(p.dst, b, j[u], dblk, dtok)) continue;
         const int64_t dof =
             (dblk * p.dst.s_blk + dtok * p.dst.s_tok + hk[u] * p.dst.s_head) * p.esize + c[u] * 16;
-        __builtin_nontemporal_store(
-            val[u], reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof));
+        *reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof) = val[u];
       }
     }
   }
@@ -207,7 +209,8 @@ __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams 
 hipError_t launch_kv_gather(const GatherParams& p, bool src_paged, bool dst_paged, hipStream_t s) {
   if (p.vec_shift >= 0 && p.head_shift >= 0) {
     const int64_t per_seq = static_cast<int64_t>(p.idx_stride) << (p.vec_shift + p.head_shift);
-    const int64_t want = (per_seq + kGatherItems * 256 - 1) / (kGatherItems * 256);
+    const int64_t per_wg = 256 * (dst_paged ? kGatherItems<true> : kGatherItems<false>);
+    const int64_t want = (per_seq + per_wg - 1) / per_wg;
     const dim3 g(static_cast<uint32_t>(want < 4096 ? want : 4096),
                  static_cast<uint32_t>(p.B < 65535 ? p.B : 65535), 2),
         blk(256);

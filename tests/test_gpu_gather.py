@@ -91,6 +91,17 @@ def test_gather_matches_oracle(case):
     assert np.array_equal(bits(dv), vref), "V draft cache differs from the oracle"
 
 
+# Lists around one workgroup's items (eight vectors a row; three items a thread into
+# contiguous rows, four into pages), one row short, full, one over, and several.
+ITEM_EDGES = [(dps, n) for dps, per in ((0, 96), (4, 128)) for n in (1, per - 1, per, per + 1, 3 * per + 5)]
+
+
+@pytest.mark.parametrize("dps,n", ITEM_EDGES)
+def test_gather_item_edges(dps, n):
+    test_gather_matches_oracle((f"items_p{dps}_n{n}", 2, 1, 64, "bf16", [700, 90], 16, dps, n,
+                                [n, n // 2]))
+
+
 def test_gather_refuses_a_short_destination():
     """A contiguous draft cache of 10 rows cannot take lists of 16: the call
     is refused before any launch (a silent drop would leave dst_lens counting

@@ -7,6 +7,8 @@
 // 1122 -> 1009, fp32 8-token 64 x 2048, G = 8 739 -> 330; two row tiles then
 // fit 256 registers, so two workgroups share a compute unit (48 x 2000: 90 ->
 // 77).  The exceptions are in attn_agpr.hip.
+#include <atomic>
+
 #include "attn_kernel.h"
 
 namespace md {
@@ -97,9 +99,33 @@ static hipError_t launch_i(const AttnParams& p, int head_dim, bool bf16, int NT,
               : launch_d<64, false, IDX>(p, NT, paged, depth, occ, n_blocks, s);
 }
 
+// The instances live in two code objects, this file's and attn_agpr.hip's, and the
+// runtime loads one at its first launch: a verify would load the one and the
+// first draft after it the other, a stall of 6 ms in the middle of a run, with
+// slower clocks for ten steps behind it (1400 -> 1250 us a verify).  So the first
+// attention call on a device loads both (asking for a kernel's attributes does).
+static void load_instances(hipStream_t s) {
+  static std::atomic<uint64_t> loaded{0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
+  const uint64_t bit = uint64_t{1} << dev;
+  if (loaded.load(std::memory_order_relaxed) & bit) return;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) {
+    hipFuncAttributes attr;
+    (void)hipFuncGetAttributes(
+        &attr, reinterpret_cast<const void*>(
+                   &attn_partial_kernel<128, true, 1, false, false, 1, 2, false, kWaves>));
+    (void)hipFuncGetAttributes(&attr, attn_agpr_kernel());
+    loaded.fetch_or(bit, std::memory_order_relaxed);
+  }
+  (void)hipGetLastError();  // a launch reports its own errors
+}
+
 hipError_t launch_attn_partial(const AttnParams& p, int head_dim, bool bf16, int NT, bool paged,
                                int depth, int occ, int64_t n_blocks, hipStream_t s) {
   if (n_blocks <= 0) return hipSuccess;
+  load_instances(s);
   if (p.mode == MD_MODE_DRAFT_INDEXED)
     return launch_i<true>(p, head_dim, bf16, NT, paged, depth, occ, n_blocks, s);
   return launch_i<false>(p, head_dim, bf16, NT, paged, depth, occ, n_blocks, s);

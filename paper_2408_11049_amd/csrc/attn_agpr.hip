@@ -12,6 +12,11 @@
 
 namespace md {
 
+const void* attn_agpr_kernel() {
+  return reinterpret_cast<const void*>(
+      &attn_partial_kernel<128, true, 2, true, false, 1, 1, true, kWaves, true>);
+}
+
 hipError_t launch_attn_agpr(const AttnParams& p, int NT, bool paged, int64_t n_blocks,
                             hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>(n_blocks)), block(kWaves * 64);

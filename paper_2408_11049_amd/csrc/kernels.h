@@ -107,6 +107,7 @@ hipError_t launch_attn_partial(const AttnParams& p, int head_dim, bool bf16, int
 // that keep their accumulators in AGPRs; see attn_agpr.hip.
 hipError_t launch_attn_agpr(const AttnParams& p, int NT, bool paged, int64_t n_blocks,
                             hipStream_t s);
+const void* attn_agpr_kernel();  // one of them, to name their code object
 
 // parts_readable: every part's O may be read, empty parts included (the
 // library's own split plans); md_merge_lse never reads an empty part's O.

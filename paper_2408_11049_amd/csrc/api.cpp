@@ -55,10 +55,10 @@ int prefetch_depth(int NT, int mode) {
   return forced ? forced : 1;
 }
 
-// Waves per SIMD targeted by the kernel instance (MD_OCCUPANCY = 1 or 2
-// overrides, for tuning sweeps).  Long verify streams with two row tiles run
-// best at one wave per SIMD (more registers, no spills); the short draft
-// calls and single-row-tile shapes at two.
+// Waves per SIMD the kernel instance is compiled for (MD_OCCUPANCY = 1 or 2
+// overrides, for tuning sweeps): two for the drafts and for one row tile.  The
+// verify of two row tiles takes the instance compiled for one, which with its
+// accumulators in VGPRs fits two workgroups on a compute unit all the same.
 int occupancy(int NT, int depth, int mode) {
   const int forced = env_knob("MD_OCCUPANCY", 1, 2);
   if (forced) return forced;

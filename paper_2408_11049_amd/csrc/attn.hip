@@ -16,15 +16,18 @@ namespace md {
 // ---------------------------------------------------------------------------
 // Host-side dispatch over the compiled instances.
 
-template <int D, bool BF16, int NT, bool IDX, int P, int OCC, bool BAL = false, int W = kWaves>
+template <int D, bool BF16, int NT, bool IDX, int P, int OCC, bool BAL = false, int W = kWaves,
+          bool CONTIGUOUS = true>
 static hipError_t launch_p(const AttnParams& p, bool paged, int64_t n_blocks, hipStream_t s) {
   dim3 grid(static_cast<uint32_t>(n_blocks)), block(W * 64);
   if (paged)
     hipLaunchKernelGGL((attn_partial_kernel<D, BF16, NT, true, IDX, P, OCC, BAL, W>), grid, block,
                        0, s, p);
-  else
+  else if constexpr (CONTIGUOUS)
     hipLaunchKernelGGL((attn_partial_kernel<D, BF16, NT, false, IDX, P, OCC, BAL, W>), grid, block,
                        0, s, p);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -41,7 +44,7 @@ static hipError_t launch_nt(const AttnParams& p, bool paged, int depth, int occ,
   if constexpr (kAgpr && NT == 2)
     if (p.bal) return launch_attn_agpr(p, NT, paged, n_blocks, s);
   if constexpr (kAgpr && NT == 3)
-    if (!paged && p.mode == MD_MODE_VERIFY && depth < 2 && p.waves == kWaves)
+    if (!paged && p.mode == MD_MODE_VERIFY && (p.bal || (depth < 2 && p.waves == kWaves)))
       return launch_attn_agpr(p, NT, paged, n_blocks, s);
   // The balanced verify: one tile in flight, the verify's default waves per
   // SIMD (two for one row tile of bf16, else one).  Compiled only where its
@@ -51,7 +54,8 @@ static hipError_t launch_nt(const AttnParams& p, bool paged, int depth, int occ,
     if (p.bal) {
       (void)depth;
       (void)occ;
-      return launch_p<D, BF16, NT, IDX, 1, (BF16 && NT == 1) ? 2 : 1, true>(p, paged, n_blocks, s);
+      return launch_p<D, BF16, NT, IDX, 1, (BF16 && NT == 1) ? 2 : 1, true, kWaves,
+                      !(kAgpr && NT == 3)>(p, paged, n_blocks, s);
     }
   } else {
     if (p.bal) return hipErrorInvalidValue;

@@ -246,7 +246,7 @@ hipError_t launch_merge_lse(int n_parts, int64_t n_rows, int head_dim, bool out_
   if (n_rows <= 0) return hipSuccess;
   dim3 grid(static_cast<uint32_t>((n_rows + 3) / 4)), block(256);
   const bool reg = parts_readable && n_parts <= kRegParts;
-  if (parts_readable && n_parts > kRegParts && n_rows <= (1 << 20)) {
+  if (parts_readable && !reg) {
     const dim3 g(static_cast<uint32_t>(n_rows)), blk(64 * kManyWaves);
 #define MD_MERGE_MANY(D, BF)                                                                 \
   hipLaunchKernelGGL((merge_many_kernel<D, BF>), g, blk, 0, s, n_parts, n_rows, o_parts,     \

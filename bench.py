@@ -63,10 +63,12 @@ PROFILE_TRACE = os.path.join(PROFILES, "attn_verify_llama8b_b64_s32k_paged_trace
 PROFILE_COUNTERS = os.path.join(PROFILES, "attn_verify_llama8b_b64_s32k_paged_counters.md")
 PROFILE_MFMA = os.path.join(PROFILES, "attn_mfma_llama8b_b64_s32k_paged.md")
 CSRC = os.path.join(ROOT, "paper_2408_11049_amd", "csrc")
-# What decides the attention launches' code and plans.
+# What decides the attention launches' code and plans: their sources, and the
+# per-file compiler flags.
 KERNEL_SOURCES = [os.path.join(CSRC, f) for f in
                   ("attn_kernel.h", "attn.hip", "attn_agpr.hip", "merge.hip", "api.cpp", "plan.cpp",
-                  "internal.h", "kernels.h")]
+                   "internal.h", "kernels.h")]
+KERNEL_SOURCES.append(os.path.join(ROOT, "paper_2408_11049_amd", "build.py"))
 # Per-config table: the workload list's configurations (the bench workload is
 # the headline itself).
 CONFIGS = ["tiny_f32", "llama8b_b32_s8k", "llama8b_b64_ragged_paged", "llama8b_b256_s8k_koutlier",

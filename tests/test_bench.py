@@ -55,6 +55,18 @@ def test_profile_readers_match_the_kernel_source(monkeypatch):
     assert bench.read_counters() is None and bench.read_mfma() is None and bench.read_trace() is None
 
 
+def test_profiles_go_stale_with_the_compiler_flags(tmp_path, monkeypatch):
+    """The register form of the attention kernels is a compiler flag in build.py:
+    another build.py makes the committed summaries stale."""
+    path = os.path.join(ROOT, "paper_2408_11049_amd", "build.py")
+    other = tmp_path / "build.py"
+    other.write_text(open(path).read().replace("-amdgpu-mfma-vgpr-form", ""))
+    assert other.read_text() != open(path).read()
+    monkeypatch.setattr(bench, "KERNEL_SOURCES",
+                        [str(other) if p == path else p for p in bench.KERNEL_SOURCES])
+    assert bench.read_counters() is None and bench.read_mfma() is None and bench.read_trace() is None
+
+
 def _trace_csv(path, names_durs):
     """A kernel-trace CSV in rocprofv3's layout: one row per dispatch."""
     import csv

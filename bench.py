@@ -1048,11 +1048,11 @@ def summarize_prefill(trace_csv, fetch_csv, write_csv, bench_json, cmd):
             "(under the profiler).",
             "",
             "Reading: both SnapKV passes read K exactly once each but run below the HBM rate:",
-            "every 64-key tile is shared by 128 observation rows (G x 32) and costs MFMA scores,",
-            "128 x 64 exponentials and, in the votes pass, a cross-row reduction per key, with",
-            "the four waves of a workgroup synchronised per tile (vector-ALU bound).  The",
-            "selection reads the votes once; its time goes to the radix passes over keys held",
-            "in registers.  The gather reads scattered 256 B rows.  All of it runs once per",
+            "a wave of the bf16 passes owns 32 rows x 32 keys of a tile that the workgroup's",
+            "waves share through LDS, and per score pays its share of an MFMA and a multiply-add,",
+            "an exponential and an add.  The selection reads the votes once; its time goes to the",
+            "radix passes over keys held in registers.  The gather reads scattered 256 B rows.",
+            "All of it runs once per",
             "prompt, at prefill."]
     return "\n".join(out) + "\n"
 

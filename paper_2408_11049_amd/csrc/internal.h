@@ -30,7 +30,8 @@ constexpr int kTile = 32;            // tokens per wave iteration
 constexpr int kMinChunkTokens = 128;  // shortest chunk of a split range: a tile per wave
 constexpr int kPlainChunkTokens = 1024;  // the same of a plain plan (make_plan)
 constexpr int64_t kWholeTokens = 512;  // ranges up to this are not split
-constexpr int64_t kWholeList = 1020;   // listed drafts: lists up to this are not split
+constexpr int64_t kWholeList = 1021;   // the same of a listed draft (list and speculated tokens)
+constexpr int64_t kBareList = 1020;    // lists up to this run without a workspace
 constexpr int kMaxRows = 64;         // G*L bound: at most four 16-row tiles
 constexpr int kPairMinChunkTokens = 4096;  // head pairs on split ranges: chunks at least this long
 constexpr int kMaxChunks = 65535;    // a split plan's arrival count fits 16 bits

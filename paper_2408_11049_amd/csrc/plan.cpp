@@ -267,13 +267,16 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // Up to kWholeTokens one pass does: 256 tokens in one chunk take 8.9-10.2 us
   // and in two 9.4-11.0; at 430-512 the kernels gain 3 us of 13 but a caller
   // issuing call after call loses 5 us of host time to the second launch (82
-  // units of 427 tokens through the binding: 17.4 us whole, 17.9 split).  A
-  // listed draft keeps lists of up to kWholeList positions whole, so that they
-  // need no workspace.
+  // units of 427 tokens through the binding: 17.4 us whole, 17.9 split).  Listed
+  // drafts cost the host more, so one pass does for longer: whole / split through
+  // the binding, one sequence of 8 KV heads, one token, 520 entries 16.5 / 21.1
+  // us, 768 18.7 / 21.0, 1020 21.0 / 21.0; five tokens, 1020 entries 27.9 / 20.8.  (Replayed from a graph, which has no host time,
+  // splits win from 520 entries on: 14.9 / 10.2, 20.8 / 10.5 at 1020.)
   const int64_t min_chunk = plain ? kPlainChunkTokens : kMinChunkTokens;
-  const int64_t whole = std::max<int64_t>(
-      plain ? kPlainChunkTokens : 0,
-      mode == MD_MODE_DRAFT_INDEXED ? kWholeList + L : kWholeTokens);
+  const bool listed = mode == MD_MODE_DRAFT_INDEXED;
+  const int64_t whole =
+      plain ? std::max<int64_t>(kPlainChunkTokens, listed ? kBareList + L : 0)
+            : (listed ? kWholeList : kWholeTokens);
   const bool bf16 = a->dtype == MD_BF16;
   const StreamCost sc = stream_cost(p.NT, a->head_dim, bf16);
   const StreamCost* cost = plain || env_knob("MD_SLOTS_SCALE", 2, 4) ? nullptr : &sc;

@@ -225,6 +225,17 @@ int main() {
   printf("balanced plans per pass: %d %d %d %d\n", bal_per_pass[0], bal_per_pass[1],
          bal_per_pass[2], bal_per_pass[3]);
 
+  // Lists of 1020 entries: whole with one token, split with five (as any range
+  // past 1021 tokens), and run without a workspace either way.
+  for (int L : {1, 2, 5, 8})
+    for (int32_t n : {512, 1016, 1020, 1021, 1024}) {
+      md_attn_args a = good_args(1, L, 32, 8, 128, 4096, 16);
+      const md::Plan p = md::make_plan(&a, MD_MODE_DRAFT_INDEXED, 0, n, 256);
+      check((p.n_chunks == 1) == (n + L <= 1021), "listed draft split", n, L);
+      a.workspace = nullptr;
+      check(n > 1020 || md::plan_call(&a, MD_MODE_DRAFT_INDEXED, 0, n, 256).workspace_bytes == 0,
+            "short lists run without a workspace", n, L);
+    }
   check(g_pairs_refused > 0, "sweep reaches split head pairs", g_pairs_refused);
   check(g_between > 0, "sweep reaches workspaces between the two plans", g_between);
 

@@ -1070,20 +1070,15 @@ static hipError_t sk_launch_f32(const SnapkvParams& p, int TW, bool paged, int64
   return hipErrorInvalidValue;
 }
 
-template <int D, int NR, int RH, int KH, int PASS>
-static hipError_t sk_launch_grid(const SnapkvParams& p, bool paged, int64_t blocks,
-                                 hipStream_t s) {
-  const bool wa = sk_wave_addresses<D, true>(p, paged);
+template <int D, int NR, int RH, int KH, bool PAGED, int PASS>
+static hipError_t sk_launch_grid(const SnapkvParams& p, int64_t blocks, hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>(blocks)), block(RH * KH * 64);
-#define MD_SK_LAUNCH(PG, WAV)                                                                 \
-  hipLaunchKernelGGL((snapkv_pass_kernel_bf16<D, NR, RH, KH, PG, WAV, PASS>), grid, block, 0, \
-                     s, p)
-  if (paged) {
-    if (wa) MD_SK_LAUNCH(true, true); else MD_SK_LAUNCH(true, false);
-  } else {
-    if (wa) MD_SK_LAUNCH(false, true); else MD_SK_LAUNCH(false, false);
-  }
-#undef MD_SK_LAUNCH
+  if (sk_wave_addresses<D, true>(p, PAGED))
+    hipLaunchKernelGGL((snapkv_pass_kernel_bf16<D, NR, RH, KH, PAGED, true, PASS>), grid, block, 0,
+                       s, p);
+  else
+    hipLaunchKernelGGL((snapkv_pass_kernel_bf16<D, NR, RH, KH, PAGED, false, PASS>), grid, block, 0,
+                       s, p);
   return hipGetLastError();
 }
 
@@ -1093,23 +1088,32 @@ static hipError_t sk_launch_grid(const SnapkvParams& p, bool paged, int64_t bloc
 // 1735 with two blocks a wave and 64 keys).  256 rows of d = 64 take two
 // blocks in four waves, since a 32-key tile is too small to load by eight.
 // Up to 32 rows two key groups share the tile, so that a workgroup keeps two
-// waves (50.5 us against 54.5 with four on 8 prompts of 8192).
-template <int D, int PASS>
-static hipError_t sk_launch_bf16(const SnapkvParams& p, bool paged, int64_t blocks, hipStream_t s) {
-  if (p.R <= 32) return sk_launch_grid<D, 1, 1, 2, PASS>(p, paged, blocks, s);
-  if (p.R <= 64) return sk_launch_grid<D, 1, 2, 1, PASS>(p, paged, blocks, s);
-  if (p.R <= 128) return sk_launch_grid<D, 1, 4, 1, PASS>(p, paged, blocks, s);
-  if constexpr (D == 128) return sk_launch_grid<D, 1, 8, 1, PASS>(p, paged, blocks, s);
-  return sk_launch_grid<D, 2, 4, 1, PASS>(p, paged, blocks, s);
+// waves (50.5 us against 54.5 with four on 8 prompts of 8192).  33-64 rows of
+// d = 64 take two key groups when paged: two waves spend too much of a 32-key
+// tile of half the bytes on its page ids and its barrier (two waves / four / the
+// earlier 16-row passes, 64 prompts of 16384, 8 heads, 508 / 446 / 462 us, 8 of
+// 8192 38.7 / 35.0 / 51.5, 4 of 6000 19.3 / 19.9 / 36.1).  Contiguous the two
+// waves win (398 / 429 / 424, 31.5 / 34.8 / 42.5), and so they do with d = 128
+// (748 / 759 / 764, 52.9 / 56.0 / 67.5 paged).
+template <int D, bool PAGED, int PASS>
+static hipError_t sk_launch_bf16(const SnapkvParams& p, int64_t blocks, hipStream_t s) {
+  constexpr bool kShort = D == 64;  // half the bytes a key
+  if (p.R <= 32) return sk_launch_grid<D, 1, 1, 2, PAGED, PASS>(p, blocks, s);
+  if (p.R <= 64) return sk_launch_grid<D, 1, 2, kShort && PAGED ? 2 : 1, PAGED, PASS>(p, blocks, s);
+  if (p.R <= 128) return sk_launch_grid<D, 1, 4, 1, PAGED, PASS>(p, blocks, s);
+  return sk_launch_grid<D, kShort ? 2 : 1, kShort ? 4 : 8, 1, PAGED, PASS>(p, blocks, s);
 }
 
 template <int PASS>
 static hipError_t sk_launch(const SnapkvParams& p, int head_dim, bool bf16, int TW, bool paged,
                             int64_t blocks, hipStream_t s) {
   if (blocks <= 0) return hipSuccess;
+  if (bf16 && paged)
+    return head_dim == 128 ? sk_launch_bf16<128, true, PASS>(p, blocks, s)
+                           : sk_launch_bf16<64, true, PASS>(p, blocks, s);
   if (bf16)
-    return head_dim == 128 ? sk_launch_bf16<128, PASS>(p, paged, blocks, s)
-                           : sk_launch_bf16<64, PASS>(p, paged, blocks, s);
+    return head_dim == 128 ? sk_launch_bf16<128, false, PASS>(p, blocks, s)
+                           : sk_launch_bf16<64, false, PASS>(p, blocks, s);
   return head_dim == 128 ? sk_launch_f32<128, PASS>(p, TW, paged, blocks, s)
                          : sk_launch_f32<64, PASS>(p, TW, paged, blocks, s);
 }

@@ -93,7 +93,7 @@ def test_votes_random(seed):
 
 # (G, n_obs, d): rows at and past each wave grid of the bf16 passes (32, 64, 128, 256 rows).
 GRID_ROWS = [(1, 32, 128), (3, 11, 128), (2, 32, 64), (5, 13, 128), (4, 32, 128), (3, 43, 64),
-             (8, 32, 128), (8, 32, 64), (1, 1, 64)]
+             (8, 32, 128), (8, 32, 64), (1, 1, 64), (3, 11, 64)]
 
 
 @pytest.mark.parametrize("G,n_obs,d", GRID_ROWS)

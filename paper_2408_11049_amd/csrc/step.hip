@@ -99,6 +99,9 @@ __device__ __forceinline__ bool cache_row(const CacheView& c, int b, int64_t j, 
   return true;
 }
 
+template <bool DST_PAGED>
+constexpr int kGatherItems = DST_PAGED ? 4 : 3;  // items per thread and iteration
+
 // One 16-byte vector per item, items ordered (vector, kv head, list slot,
 // sequence, K/V): the kv heads of one destination row are written side by
 // side (one whole token row), each read from its own listed source row.
@@ -144,16 +147,10 @@ __global__ void __launch_bounds__(256) kv_gather_kernel(const GatherParams p) {
 // thread takes several items per iteration and issues their list reads, then
 // their row loads, then their stores, so the dependent reads of one item (list
 // entry, page id, row) overlap those of the others: three items into contiguous
-// rows, four into pages.  Bounded by HBM, read and write mixed (a plain copy
-// moves 4.8 TB/s).  2049 rows of 8 heads, pages to contiguous rows, three / four
-// items: after a 1 GiB read 64 sequences 190.6 / 192.1 us; call after call 32
-// sequences 94.6 / 96.7, 64 sequences 208 / 216; into pages 257 / 239.  Stores
-// around the caches instead: 203.8, 102, 201, and into pages 254 / 234; they win
-// only where calls follow each other and the rows outgrow the last-level cache.
-template <bool DST_PAGED>
-constexpr int kGatherItems = DST_PAGED ? 4 : 3;  // items per thread and iteration
-
-template <bool SRC_PAGED, bool DST_PAGED>
+// rows, four into pages (64 sequences into pages: 250 us with three, 231 with
+// four).  Bounded by HBM, read and write mixed (a plain copy moves 4.8 TB/s).
+// AROUND: the rows are stored around the caches.
+template <bool SRC_PAGED, bool DST_PAGED, bool AROUND>
 __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams p) {
   constexpr int U = kGatherItems<DST_PAGED>;  // their loads overlap
   const bool is_v = blockIdx.z != 0;
@@ -200,28 +197,51 @@ __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams 
         if (!in[u] || !cache_row<DST_PAGED>(p.dst, b, j[u], dblk, dtok)) continue;
         const int64_t dof =
             (dblk * p.dst.s_blk + dtok * p.dst.s_tok + hk[u] * p.dst.s_head) * p.esize + c[u] * 16;
-        *reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof) = val[u];
+        u32x4* row = reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof);
+        if constexpr (AROUND)
+          __builtin_nontemporal_store(val[u], row);
+        else
+          *row = val[u];
       }
     }
   }
 }
 
+// Rows that outgrow the 256 MiB last-level cache are stored around it: through
+// it, this launch ends earlier by what it leaves dirty there, and the launches
+// behind it wait for the write-back.  Measured, through / around the caches,
+// 2049 rows of 8 heads, pages to contiguous rows, 32768-token prompts:
+//   votes, selection and gather in series, 64 prompts (537 MB of rows) 2049 /
+//     2018 us, 32 (269 MB) 1043 / 1031, 28 (235 MB) 843 / 847, 16 533 / 537
+//   selection and gather, 273 / 258, 138.6 / 132.1, 113.7 / 120.1, 78.4 / 81.8
+//   the gather by itself after a 1 GiB read 189 / 202, 97 / 105, 87 / 93, 54 / 57
+// and into pages, selection and gather, 301 / 290, 150.4 / 148.2, 126 / 134.
+constexpr int64_t kLastLevelCache = int64_t{256} << 20;
+
+template <bool SRC_PAGED, bool DST_PAGED>
+static void launch_gather_pow2(const GatherParams& p, hipStream_t s) {
+  const int64_t per_seq = static_cast<int64_t>(p.idx_stride) << (p.vec_shift + p.head_shift);
+  constexpr int64_t kPerWg = 256 * kGatherItems<DST_PAGED>;
+  const int64_t want = (per_seq + kPerWg - 1) / kPerWg;
+  const dim3 g(static_cast<uint32_t>(want < 4096 ? want : 4096),
+               static_cast<uint32_t>(p.B < 65535 ? p.B : 65535), 2),
+      blk(256);
+  if (p.n_items > kLastLevelCache / 16)
+    hipLaunchKernelGGL((kv_gather_pow2_kernel<SRC_PAGED, DST_PAGED, true>), g, blk, 0, s, p);
+  else
+    hipLaunchKernelGGL((kv_gather_pow2_kernel<SRC_PAGED, DST_PAGED, false>), g, blk, 0, s, p);
+}
+
 hipError_t launch_kv_gather(const GatherParams& p, bool src_paged, bool dst_paged, hipStream_t s) {
   if (p.vec_shift >= 0 && p.head_shift >= 0) {
-    const int64_t per_seq = static_cast<int64_t>(p.idx_stride) << (p.vec_shift + p.head_shift);
-    const int64_t per_wg = 256 * (dst_paged ? kGatherItems<true> : kGatherItems<false>);
-    const int64_t want = (per_seq + per_wg - 1) / per_wg;
-    const dim3 g(static_cast<uint32_t>(want < 4096 ? want : 4096),
-                 static_cast<uint32_t>(p.B < 65535 ? p.B : 65535), 2),
-        blk(256);
     if (src_paged && dst_paged)
-      hipLaunchKernelGGL((kv_gather_pow2_kernel<true, true>), g, blk, 0, s, p);
+      launch_gather_pow2<true, true>(p, s);
     else if (src_paged)
-      hipLaunchKernelGGL((kv_gather_pow2_kernel<true, false>), g, blk, 0, s, p);
+      launch_gather_pow2<true, false>(p, s);
     else if (dst_paged)
-      hipLaunchKernelGGL((kv_gather_pow2_kernel<false, true>), g, blk, 0, s, p);
+      launch_gather_pow2<false, true>(p, s);
     else
-      hipLaunchKernelGGL((kv_gather_pow2_kernel<false, false>), g, blk, 0, s, p);
+      launch_gather_pow2<false, false>(p, s);
     return hipGetLastError();
   }
   const int64_t want = (p.n_items + 255) / 256;

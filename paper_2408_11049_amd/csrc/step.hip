@@ -99,9 +99,6 @@ __device__ __forceinline__ bool cache_row(const CacheView& c, int b, int64_t j, 
   return true;
 }
 
-template <bool DST_PAGED>
-constexpr int kGatherItems = DST_PAGED ? 4 : 3;  // items per thread and iteration
-
 // One 16-byte vector per item, items ordered (vector, kv head, list slot,
 // sequence, K/V): the kv heads of one destination row are written side by
 // side (one whole token row), each read from its own listed source row.
@@ -140,6 +137,9 @@ __global__ void __launch_bounds__(256) kv_gather_kernel(const GatherParams p) {
   }
 }
 
+template <bool DST_PAGED>
+constexpr int kGatherItems = DST_PAGED ? 4 : 3;  // items per thread and iteration
+
 // The same copy when row_vecs and Hkv are powers of two: grid (items of one
 // sequence, sequences, K/V), each sequence's items in the order above, so an
 // item's (list slot, kv head, vector) are shifts and masks of its index
@@ -147,10 +147,18 @@ __global__ void __launch_bounds__(256) kv_gather_kernel(const GatherParams p) {
 // thread takes several items per iteration and issues their list reads, then
 // their row loads, then their stores, so the dependent reads of one item (list
 // entry, page id, row) overlap those of the others: three items into contiguous
-// rows, four into pages (64 sequences into pages: 250 us with three, 231 with
-// four).  Bounded by HBM, read and write mixed (a plain copy moves 4.8 TB/s).
-// AROUND: the rows are stored around the caches.
-template <bool SRC_PAGED, bool DST_PAGED, bool AROUND>
+// rows, four into pages.  Bounded by HBM, read and write mixed (a plain copy
+// moves 4.8 TB/s).  The rows are stored around the caches: nothing reads them
+// before the next draft step, and through the caches up to 256 MiB of them stay
+// behind dirty, which the next launches have to write back.  2049 rows of 8 heads,
+// pages to contiguous rows, each call to rows of its own, through the caches with
+// three items / around them with three / with four: 4 sequences 18.0 / 16.8 / 18.0
+// us, 16 56.2 / 52.7 / 54.2, 32 107.0 / 101.1 / 103.0, 64 208 / 199 / 202; votes,
+// selection and gather of 64 prompts 2028 / 1998 / 2002.  Into pages, through with
+// four / around with three / with four: 16 62.3 / 64.2 / 60.5, 64 236 / 250 / 231.
+// (One gather right after a 1 GiB read ends earlier through the caches, 64 189 us
+// against 202, by the write-back it leaves behind.)
+template <bool SRC_PAGED, bool DST_PAGED>
 __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams p) {
   constexpr int U = kGatherItems<DST_PAGED>;  // their loads overlap
   const bool is_v = blockIdx.z != 0;
@@ -197,26 +205,12 @@ __global__ void __launch_bounds__(256) kv_gather_pow2_kernel(const GatherParams 
         if (!in[u] || !cache_row<DST_PAGED>(p.dst, b, j[u], dblk, dtok)) continue;
         const int64_t dof =
             (dblk * p.dst.s_blk + dtok * p.dst.s_tok + hk[u] * p.dst.s_head) * p.esize + c[u] * 16;
-        u32x4* row = reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof);
-        if constexpr (AROUND)
-          __builtin_nontemporal_store(val[u], row);
-        else
-          *row = val[u];
+        __builtin_nontemporal_store(
+            val[u], reinterpret_cast<u32x4*>((is_v ? p.dst.v : p.dst.k) + dof));
       }
     }
   }
 }
-
-// Rows that outgrow the 256 MiB last-level cache are stored around it: through
-// it, this launch ends earlier by what it leaves dirty there, and the launches
-// behind it wait for the write-back.  Measured, through / around the caches,
-// 2049 rows of 8 heads, pages to contiguous rows, 32768-token prompts:
-//   votes, selection and gather in series, 64 prompts (537 MB of rows) 2049 /
-//     2018 us, 32 (269 MB) 1043 / 1031, 28 (235 MB) 843 / 847, 16 533 / 537
-//   selection and gather, 273 / 258, 138.6 / 132.1, 113.7 / 120.1, 78.4 / 81.8
-//   the gather by itself after a 1 GiB read 189 / 202, 97 / 105, 87 / 93, 54 / 57
-// and into pages, selection and gather, 301 / 290, 150.4 / 148.2, 126 / 134.
-constexpr int64_t kLastLevelCache = int64_t{256} << 20;
 
 template <bool SRC_PAGED, bool DST_PAGED>
 static void launch_gather_pow2(const GatherParams& p, hipStream_t s) {
@@ -226,10 +220,7 @@ static void launch_gather_pow2(const GatherParams& p, hipStream_t s) {
   const dim3 g(static_cast<uint32_t>(want < 4096 ? want : 4096),
                static_cast<uint32_t>(p.B < 65535 ? p.B : 65535), 2),
       blk(256);
-  if (p.n_items > kLastLevelCache / 16)
-    hipLaunchKernelGGL((kv_gather_pow2_kernel<SRC_PAGED, DST_PAGED, true>), g, blk, 0, s, p);
-  else
-    hipLaunchKernelGGL((kv_gather_pow2_kernel<SRC_PAGED, DST_PAGED, false>), g, blk, 0, s, p);
+  hipLaunchKernelGGL((kv_gather_pow2_kernel<SRC_PAGED, DST_PAGED>), g, blk, 0, s, p);
 }
 
 hipError_t launch_kv_gather(const GatherParams& p, bool src_paged, bool dst_paged, hipStream_t s) {

@@ -102,14 +102,10 @@ def test_gather_item_edges(dps, n):
                                 [n, n // 2]))
 
 
-# Draft caches of exactly 256 MiB (K and V: 2 x 2 sequences x rows x 128 B) and a row
-# more, stored through and around the last-level cache; one list goes past what an
-# iteration of the grid covers (4096 workgroups of 96 rows).
-@pytest.mark.parametrize("dps,rows,n", [(0, 524288, 3001), (0, 524289, 4096 * 96 + 37),
-                                        (16, 524288, 3001), (16, 524304, 3001)])
-def test_gather_around_the_cache(dps, rows, n):
-    test_gather_matches_oracle((f"llc_p{dps}_r{rows}", 2, 1, 64, "bf16", [700, 90], 16, dps, rows,
-                                [n, 97]))
+def test_gather_past_one_iteration():
+    """A list longer than one iteration of the grid covers (4096 workgroups of 96 rows)."""
+    test_gather_matches_oracle(("grid", 2, 1, 64, "bf16", [700, 90], 16, 0, 4096 * 96 + 40,
+                                [4096 * 96 + 37, 97]))
 
 
 def test_gather_refuses_a_short_destination():

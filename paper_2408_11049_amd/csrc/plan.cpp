@@ -140,15 +140,16 @@ static double launch_us(const StreamCost& c, int32_t wgs, double bytes, int32_t 
 // The range split for n_groups workgroups' worth of units of U tokens.  The
 // plain rule gives a group one chunk when the groups alone cover every compute
 // unit, else just as many as cover them, never below `min_chunk` tokens
-// per chunk (kMinChunkTokens, a tile for each wave: a 5-token verify of one 4001-token sequence
-// takes 27.7 us in 1024-token chunks, 16.2 in 256 and 15.0 in 128); a range of
-// at most `whole` tokens is not cut.  That leaves a second round of few
+// per chunk (kMinChunkTokens, a tile for each wave: a 5-token verify of one
+// 4001-token sequence takes 27.7 us in 1024-token chunks, 16.2 in 256 and 15.0
+// in 128); a range of at most `whole` tokens is not cut.  That leaves a second round of few
 // workgroups wherever the groups do not divide the compute units (40 sequences
 // of 8 heads and 3000 tokens: 64 of 320 workgroups run alone), so any other
 // count that the launch cost above puts at 5% less is taken instead.
 static void split_units(int64_t U, int64_t n_groups, int64_t slots, int64_t whole,
-                        int64_t min_chunk, const StreamCost* cost, int64_t group_rows, int64_t tok_bytes, int d,
-                        int64_t* n_chunks_out, int64_t* chunk_len_out) {
+                        int64_t min_chunk, const StreamCost* cost, int64_t group_rows,
+                        int64_t tok_bytes, int d, int64_t* n_chunks_out,
+                        int64_t* chunk_len_out) {
   int64_t n_chunks = 1;
   const int64_t cap = U <= whole ? 1 : ceil_div(U, min_chunk);
   if (n_groups > 0 && n_groups < slots) n_chunks = std::min(ceil_div(slots, n_groups), cap);
@@ -270,8 +271,9 @@ Plan make_plan(const md_attn_args* a, int mode, int n_sink, int window, int num_
   // units of 427 tokens through the binding: 17.4 us whole, 17.9 split).  Listed
   // drafts cost the host more, so one pass does for longer: whole / split through
   // the binding, one sequence of 8 KV heads, one token, 520 entries 16.5 / 21.1
-  // us, 768 18.7 / 21.0, 1020 21.0 / 21.0; five tokens, 1020 entries 27.9 / 20.8.  (Replayed from a graph, which has no host time,
-  // splits win from 520 entries on: 14.9 / 10.2, 20.8 / 10.5 at 1020.)
+  // us, 768 18.7 / 21.0, 1020 21.0 / 21.0; five tokens, 1020 entries 27.9 / 20.8.
+  // (Replayed from a graph, which has no host time, splits win from 520 entries
+  // on: 14.9 / 10.2, 20.8 / 10.5 at 1020.)
   const int64_t min_chunk = plain ? kPlainChunkTokens : kMinChunkTokens;
   const bool listed = mode == MD_MODE_DRAFT_INDEXED;
   const int64_t whole =
@@ -421,7 +423,9 @@ void split_range_plain(int64_t U, int64_t n_units, int64_t wgs, int32_t* n_chunk
 // d = 128) or its bytes, whichever takes longer.  start_us grows with the rows
 // of Q a workgroup loads: 50 fp32 units of 256 rows take 258 us in 250
 // workgroups, one round, and 322 in 1000.  Residency as the registers and LDS of
-// the pass instances allow.
+// the pass instances allow.  At 33-64 rows of bf16 the counts chosen take no more
+// than 3% over the best of a sweep of counts (one to 128 prompts of 2000 to 32768
+// tokens, both head dims, paged and contiguous: 44 shapes), 5% at one.
 PassCost pass_cost(int R, int d, bool f32) {
   const double rows = R / 128.0, wide = d / 128.0;
   PassCost c;

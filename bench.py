@@ -354,7 +354,8 @@ def summarize_mfma(csv_path, bench_json, cmd):
     rec = _bench_line(bench_json)
     W, K, S0 = rec["warmup"], rec["steps"], settle_count(rec)
     cfg = rec["config"]
-    ver, dra = timed_calls(_dispatches(_rows(csv_path)), W, K, S0)
+    ds = _dispatches(_rows(csv_path))
+    ver, dra = timed_calls(ds, W, K, S0)
     tr = read_trace()
     out = ["# MFMA use of the bench's verify and draft calls (rocprofv3 counters)",
            "",
@@ -392,6 +393,21 @@ def summarize_mfma(csv_path, bench_json, cmd):
                    f"{mean:.2f} | {tf:.1f} | {tf / MFMA_BF16_PEAK_TFLOPS:.4f} | {ut:.2f} |")
         fields.update({f"{name}_mfma_flop_per_launch": f"{fl:.6e}",
                        f"{name}_mfma_tflops": round(tf, 2), f"{name}_mfma_busy_pct": round(ut, 3)})
+    passes = {}
+    for d in ds:
+        if "snapkv_pass_kernel" in d["name"]:
+            passes.setdefault(_short(d["name"]), []).append(d)
+    if passes:
+        out += ["", "The SnapKV passes of the same run (64 prompts of 32768 tokens, 128 observation rows a",
+                "kv head; 2 FLOP x d per row and key), means over every dispatch, the rate by the",
+                "dispatch's own duration under the counters:", "",
+                "| kernel | dispatches | FLOP per launch | us | bf16 TFLOP/s | MfmaUtil % |",
+                "|---|---|---|---|---|---|"]
+        for k, dl in passes.items():
+            fl = sum(d.get("MfmaFlopsBF16", 0.0) for d in dl) / len(dl)
+            us = sum(d["end"] - d["start"] for d in dl) / len(dl) / 1e3
+            ut = sum(d.get("MfmaUtil", 0.0) for d in dl) / len(dl)
+            out.append(f"| `{k}` | {len(dl)} | {fl:.4e} | {us:.1f} | {fl / us / 1e6:.1f} | {ut:.2f} |")
     out += ["", "Fields read by bench.py (`roofline.mfma`), valid while the kernel sources hash to",
             "kernel_source_sha256:", ""]
     out += [f"{k}: {v}" for k, v in fields.items()]
@@ -1051,9 +1067,9 @@ def summarize_prefill(trace_csv, fetch_csv, write_csv, bench_json, cmd):
             "a wave of the bf16 passes owns 32 rows x 32 keys of a tile that the workgroup's",
             "waves share through LDS, and per score pays its share of an MFMA and a multiply-add,",
             "an exponential and an add.  The selection reads the votes once; its time goes to the",
-            "radix passes over keys held in registers.  The gather reads scattered 256 B rows.",
-            "All of it runs once per",
-            "prompt, at prefill."]
+            "radix passes over keys held in registers.  The gather reads scattered 256 B rows and",
+            "stores them around the caches, so that nothing is left for the next launch to write",
+            "back.  All of it runs once per prompt, at prefill."]
     return "\n".join(out) + "\n"
 
 
@@ -1197,13 +1213,13 @@ ISSUE_COUNTERS = ["SQ_WAVES", "SQ_WAVE_CYCLES", "SQ_WAIT_ANY", "SQ_WAIT_INST_ANY
                   "SQ_BUSY_CYCLES", "GRBM_GUI_ACTIVE"]
 
 
-def summarize_issue(csv_path, bench_json, cmd, num_cus=256):
+def summarize_issue(csv_path, bench_json, cmd, num_cus=256, num_xcds=8):
     """Where the waves of the SnapKV passes (and, for reference, the bench's
     verify and draft) spend their time: wave-cycles waiting for anything
     (a dependency: memory, LDS, a barrier) against waiting to issue (a ready
-    instruction held back by a busy unit), the VALU busy fraction as
-    rocprofv3's VALUBusy defines it, and VALU and transcendental instructions
-    per wave, from one --pmc pass over a bench run."""
+    instruction held back by a busy unit), the VALU busy fraction, VALU and
+    transcendental instructions per wave and the clock, from one --pmc pass over
+    a bench run.  GRBM_GUI_ACTIVE arrives summed over the XCDs."""
     rec = _bench_line(bench_json)
     W, K, S0 = rec["warmup"], rec["steps"], settle_count(rec)
     ds = _dispatches(_rows(csv_path))
@@ -1227,20 +1243,23 @@ def summarize_issue(csv_path, bench_json, cmd, num_cus=256):
            "wait (any) = SQ_WAIT_ANY / SQ_WAVE_CYCLES: the share of wave time spent waiting on",
            "a dependency (memory, LDS, a barrier); wait (issue) = SQ_WAIT_INST_ANY /",
            "SQ_WAVE_CYCLES: the share spent with an instruction ready but not issued (a busy",
-           "unit); VALU busy = 100 x SQ_ACTIVE_INST_VALU / CUs / GRBM_GUI_ACTIVE (rocprofv3's",
-           "VALUBusy, quad-cycle units as it reports them).",
+           f"unit); cycles = GRBM_GUI_ACTIVE / {num_xcds} (it is reported summed over the XCDs); VALU",
+           "busy = 100 x SQ_ACTIVE_INST_VALU / CUs / cycles (SQ_ACTIVE_INST_VALU counts quad-",
+           "cycles of four SIMDs); clock = cycles / the dispatch's duration under the profiler.",
            "",
-           "| kernel | dispatches | waves | wait (any) | wait (issue) | VALU busy % | VALU insts / wave | transcendental / wave |",
-           "|---|---|---|---|---|---|---|---|"]
+           "| kernel | dispatches | waves | wait (any) | wait (issue) | VALU busy % | VALU insts / wave | transcendental / wave | clock GHz |",
+           "|---|---|---|---|---|---|---|---|---|"]
     for name, dl in sorted(groups.items(), key=lambda kv: -sum(d.get("SQ_WAVE_CYCLES", 0) for d in kv[1])):
         m = {c: sum(d.get(c, 0.0) for d in dl) / len(dl) for c in ISSUE_COUNTERS}
+        cycles = m["GRBM_GUI_ACTIVE"] / num_xcds or 1.0
+        ns = sum(d["end"] - d["start"] for d in dl) / len(dl)
         wc = m["SQ_WAVE_CYCLES"] or 1.0
         waves = m["SQ_WAVES"] or 1.0
-        busy = 100.0 * m["SQ_ACTIVE_INST_VALU"] / num_cus / (m["GRBM_GUI_ACTIVE"] or 1.0)
+        busy = 100.0 * m["SQ_ACTIVE_INST_VALU"] / num_cus / cycles
         label = (role[name] + " " if name in role else "") + f"`{_short(name)}`"
         out.append(f"| {label} | {len(dl)} | {m['SQ_WAVES']:.0f} | {m['SQ_WAIT_ANY'] / wc:.3f} | "
                    f"{m['SQ_WAIT_INST_ANY'] / wc:.3f} | {busy:.1f} | {m['SQ_INSTS_VALU'] / waves:.0f} | "
-                   f"{m['SQ_INSTS_VALU_TRANS_F32'] / waves:.0f} |")
+                   f"{m['SQ_INSTS_VALU_TRANS_F32'] / waves:.0f} | {cycles / ns:.2f} |")
     snap = os.path.join(ROOT, "paper_2408_11049_amd", "csrc", "snapkv.hip")
     out += ["", f"kernel_source_sha256: {kernel_source_sha256()}",
             f"snapkv_source_sha256: {kernel_source_sha256([snap])}"]

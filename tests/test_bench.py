@@ -339,10 +339,11 @@ def test_issue_summary(tmp_path):
     path = tmp_path / "c.csv"
     with open(path, "w", newline="") as f:
         w = csv.writer(f)
-        w.writerow(["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value"])
+        w.writerow(["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value",
+                    "Start_Timestamp", "End_Timestamp"])
         for i, n in enumerate(seq):
             for c, v in zip(bench.ISSUE_COUNTERS, ctr[n]):
-                w.writerow([i + 1, n, c, v])
+                w.writerow([i + 1, n, c, v, 1000 * i, 1000 * i + 50])
     bj = tmp_path / "b.json"
     bj.write_text(json.dumps({"metric": "m", "value": 1, "unit": "GB/s", "steps": 1, "warmup": 1,
                               "detail": {}}) + "\n")
@@ -352,6 +353,7 @@ def test_issue_summary(tmp_path):
     by = {("verify" if "verify (bench)" in r else "draft" if "draft (bench)" in r else "pass0"): r
           for r in rows}
     cells = [c.strip() for c in by["pass0"].split("|")[1:-1]]
-    assert cells[1:] == ["2", "100", "0.400", "0.350", "0.1", "50", "7"]  # busy: 100 x 136 / 256 / 1000
+    # GUI_ACTIVE is a sum over eight XCDs, 125 cycles: busy 100 x 136 / 256 / 125, clock 125 / 50 ns
+    assert cells[1:] == ["2", "100", "0.400", "0.350", "0.4", "50", "7", "2.50"]
     assert by["draft"].split("|")[5].strip() == "0.370"
     assert "kernel_source_sha256:" in text and "snapkv_source_sha256:" in text

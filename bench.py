@@ -195,7 +195,7 @@ def attention_calls(dispatches):
         if "attn_partial_kernel" in d["name"]:
             cur = [d]
             calls.append(cur)
-        elif "merge_lse_kernel" in d["name"] and cur is not None:
+        elif ("merge_lse_kernel" in d["name"] or "merge_many_kernel" in d["name"]) and cur is not None:
             cur.append(d)
             cur = None
         else:

@@ -319,6 +319,15 @@ def test_steps_summary_groups_by_grid(tmp_path):
     assert "bench_copy" not in text
 
 
+def test_attention_calls_count_either_merge():
+    """A split call owns the merge behind it, whichever kernel that is."""
+    names = ["md::attn_partial_kernel<a>", "md::merge_many_kernel<128, true>",
+             "md::attn_partial_kernel<a>", "md::merge_lse_kernel<128, true, true>",
+             "md::attn_partial_kernel<a>"]
+    calls = bench.attention_calls([{"name": n} for n in names])
+    assert [[d["name"] for d in c] for c in calls] == [names[:2], names[2:4], names[4:]]
+
+
 def test_issue_summary(tmp_path):
     """--summarize issue: per-instance means of the SQ issue and wait counters
     for the SnapKV passes and the bench's timed verify and draft; the wait

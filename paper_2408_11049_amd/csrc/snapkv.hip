@@ -367,13 +367,13 @@ snapkv_pass_kernel(const SnapkvParams p) {
   }
 }
 
-// The bf16 passes.  Bounded by vector issue, not by HBM: per (row, key) score
-// the method costs a multiply-add, an exponential and an add, next to one
-// read of 2 d bytes per key.  So a wave owns a large block of scores per tile
-// (32 NR rows x 32 keys on v_mfma_f32_32x32x16_bf16) and the work around the
-// scores -- K staging, LDS reads, addresses, the barrier -- is paid once for
-// all of them.  RH row groups x KH key groups of waves share each tile of
-// 32 KH keys, so a K row is read from LDS by RH waves (16-row tiles with
+// The bf16 passes.  Bounded by the vector and the matrix units, not by HBM:
+// per (row, key) score the method costs a multiply-add, an exponential and an
+// add, next to one read of 2 d bytes per key.  So a wave owns a large block of
+// scores per tile (32 NR rows x 32 keys on v_mfma_f32_32x32x16_bf16) and the
+// work around the scores -- K staging, LDS reads, addresses, the barrier -- is
+// paid once for all of them.  RH row groups x KH key groups of waves share each
+// tile of 32 KH keys, so a K row is read from LDS by RH waves (16-row tiles with
 // every wave reading every key: by eight), and rows padded to an odd multiple
 // of 16 B leave the 32-row operand reads free of bank conflicts.
 //   PASS 0 computes S^T = K Q^T: a lane holds one query row per 32-row block
@@ -387,9 +387,11 @@ snapkv_pass_kernel(const SnapkvParams p) {
 // conflicts): 64 prompts of 32768 tokens, 128 rows, 1819 -> 1710 us; four
 // prompts of 5000-12000 tokens, 256 rows, 92 -> 67 us; 8 prompts of 8192, 32
 // rows, 65 -> 52 us.  On the full batch the load stream alone takes 680 us a
-// pass and the whole pass ~850: the clock drops under the matrix work (1.5 GHz
-// measured), so waves of two row blocks, which halve the LDS reads, or a third
-// of the workgroup's waves less change nothing (1720-1760 us).
+// pass and the whole pass 850-1000.  Counters there, PASS 0 / 1: vector ALU busy
+// 62 / 54% of the cycles, matrix cores 36 / 35%, no LDS conflicts, 1.55 GHz (the
+// clock drops under the matrix work): the two kinds of work alternate more than
+// they overlap, and waves of two row blocks, which halve the LDS reads, or a
+// third of the workgroup's waves less change nothing (1720-1760 us).
 template <int D, int NR, int RH, int KH, bool PAGED, bool WA, int PASS>
 __global__ void __launch_bounds__(RH * KH * 64) __attribute__((amdgpu_waves_per_eu(2)))
 snapkv_pass_kernel_bf16(const SnapkvParams p) {

@@ -115,15 +115,17 @@ static void load_instances(hipStream_t s) {
   const uint64_t bit = uint64_t{1} << dev;
   if (loaded.load(std::memory_order_relaxed) & bit) return;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) {
+  hipError_t e = hipStreamIsCapturing(s, &capture);
+  if (e == hipSuccess && capture == hipStreamCaptureStatusNone) {
     hipFuncAttributes attr;
-    (void)hipFuncGetAttributes(
+    e = hipFuncGetAttributes(
         &attr, reinterpret_cast<const void*>(
                    &attn_partial_kernel<128, true, 1, false, false, 1, 2, false, kWaves>));
-    (void)hipFuncGetAttributes(&attr, attn_agpr_kernel());
+    if (e == hipSuccess) e = hipFuncGetAttributes(&attr, attn_agpr_kernel());
     loaded.fetch_or(bit, std::memory_order_relaxed);
   }
-  (void)hipGetLastError();  // a launch reports its own errors
+  // A launch reports its own errors; one that was pending before is the caller's.
+  if (e != hipSuccess) (void)hipGetLastError();
 }
 
 hipError_t launch_attn_partial(const AttnParams& p, int head_dim, bool bf16, int NT, bool paged,

@@ -108,7 +108,7 @@ def test_votes_wave_grids(G, n_obs, d):
 
 
 def test_votes_with_a_coarse_cuts_workspace():
-    """A workspace an eighth of the query's answer holds the coarse cut of one
+    """A workspace a sixth of the query's answer holds the coarse cut of one
     prompt; its votes are those of the best cut to the rounding of fp32 sums."""
     c = wl.make_case(B=1, q_len=1, Hq=32, Hkv=8, d=128, kv_lens=[4001], dtype="bf16", page_size=16,
                      seed=905, device=DEV)

@@ -177,6 +177,17 @@ int main() {
   }
   check(md::validate_attn(nullptr, 0, 0, 1) == MD_ERR_INVALID_ARG, "null args");
 
+  // ---- verifies whose groups leave compute units idle: short ones run whole,
+  // and balanced where that costs less than the idle units
+  {
+    const md_attn_args brief = good_args(53, 3, 32, 4, 128, 5910, 0);
+    const md::Plan pb = md::make_plan(&brief, MD_MODE_VERIFY, 0, 1, 256);
+    check(!pb.bal && pb.n_chunks == 1, "53 x 4 heads of 5910 tokens run whole", pb.bal, pb.n_chunks);
+    const md_attn_args longer = good_args(86, 6, 28, 4, 128, 8309, 16);
+    const md::Plan pl = md::make_plan(&longer, MD_MODE_VERIFY, 0, 1, 256);
+    check(pl.bal, "86 x 4 heads of 8309 tokens are balanced", pl.n_chunks);
+  }
+
   // ---- extreme but valid sizes: plans stay within their invariants
   const int64_t lens[] = {1, 5, 31, 32, 33, 1023, 1024, 4096, 8192, 32768, 131072, 1 << 20,
                           static_cast<int64_t>(md::kMaxPosition)};

@@ -41,6 +41,12 @@ CASES = [
     ("bf16_two_sequences", 2, 4, 256, 256, 64, [4100, 9000], "bf16", 0, False),
     ("bf16_forced_tiny_groups", 256, 2, 8, 2, 128, [2 + (i * 53) % 300 for i in range(256)],
      "bf16", 16, True),
+    # Pairs of heads that leave compute units idle: balanced by choice where the
+    # stream is long, and (forced here) whole by choice where it is short.
+    ("bf16_rows42_172_pairs", 86, 6, 28, 4, 128, [8309 - (i * 53) % 3000 for i in range(86)],
+     "bf16", 16, False),
+    ("bf16_rows24_106_pairs", 53, 3, 32, 4, 128, [5910 - (i * 37) % 1200 for i in range(53)],
+     "bf16", 0, True),
 ]
 
 
